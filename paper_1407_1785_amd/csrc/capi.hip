@@ -412,7 +412,21 @@ SweepStats run_svt(tsvd_handle h, const Geometry& g, const SvtBuffers<T>& sb, in
             vc = 1 - vc;
             warm->vcur = vc;
         }
-        // pre-rotate: work = A V_prev
+    }
+    // A cold SVD outside the ADMM loops (whose later SVDs start warm) takes
+    // its start V from the pivoted QR of seed.hip, in FP64: there the first
+    // sweeps of V = I are many (25-29 on smooth data, 10 on noise, against 7-8),
+    // in the FP32 form they are 9 against 7, which the QR would cost.
+    bool seeded = false;
+    if constexpr (sizeof(T) == 8) {
+        if (!warm && env_int("TSVD_SEED", 1) != 0 && jacobi_seed_fits(g.m, g.n)) {
+            prof_launch(h, K_OTHER, 0.0, [&] { launch_jacobi_seed(sb.A, sb.V[vc], sb.G, g.m, g.n, g.h, st); });
+            launch_check("jacobi_seed");
+            seeded = true;
+        }
+    }
+    if (use_warm || seeded) {
+        // pre-rotate: work = A V
         ZGemmArgs<T> ga{};
         ga.A = sb.A; ga.B = sb.V[vc]; ga.C = sb.Z;
         ga.M = g.m; ga.N = g.n; ga.K = g.n;
@@ -431,7 +445,7 @@ SweepStats run_svt(tsvd_handle h, const Geometry& g, const SvtBuffers<T>& sb, in
     ja.m = g.m;
     ja.n = g.n;
     ja.h = g.h;
-    ja.reset_v = use_warm ? 0 : 1;
+    ja.reset_v = use_warm || seeded ? 0 : 1;
     ja.ctrl = h->ctrl;
     int bw = env_int("TSVD_JACOBI_BW", 0);
     if (bw != 4 && bw != 8 && bw != 16) bw = jacobi_block_width(g.m, g.n, sizeof(T), g.h);

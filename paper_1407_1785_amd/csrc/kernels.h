@@ -293,6 +293,11 @@ struct TallPlan {
 TallPlan jacobi_tall_plan(int m, int n, int h);
 template <typename T>
 void launch_jacobi_tall_round(const JacArgs<T>& a, const TallPlan& t, double* part, hipStream_t st);
+// Start V of a cold FP64 SVD (seed.hip): V = Q of the pivoted QR of A^H, per
+// slice; G is n x n scratch per slice.
+bool jacobi_seed_fits(int m, int n);
+void launch_jacobi_seed(const cplx<double>* A, cplx<double>* V, cplx<double>* G, int m, int n, int h,
+                        hipStream_t st);
 // LDS bytes one workgroup may use on the current device
 void jacobi_set_lds_limit(size_t bytes);
 
