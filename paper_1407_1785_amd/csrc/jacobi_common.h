@@ -158,40 +158,56 @@ __device__ __forceinline__ PRot prot(double al, double be, double gr, double gi,
     return prot_params<T>(al, be, gr, gi, g2);
 }
 
-// Partial sums over the first K row groups (the slice rows; the V rows
-// below them take part in the rotations only), as chains of fused
-// multiply-adds.  The number of slice row
-// groups ka is a runtime value: a uniform branch picks the unrolled
-// instance, so no per-row select is needed.
+// Sums over the first ka row groups (the slice rows; the V rows below them
+// take part in the rotations only), as chains of fused multiply-adds.  ka is
+// a runtime value, at least kMinSliceGroups(RPT) (m >= n and RPT is at most
+// the next instance above the row groups needed): the groups up to there are
+// summed without a test, each one above behind a uniform branch.
+__host__ __device__ constexpr int kMinSliceGroups(int rpt) { return rpt > 17 ? 9 : (rpt + 1) / 2; }
+
 template <typename T, int RPT, int K>
-__device__ __forceinline__ void dot_first(const cplx<T> (&x)[RPT], const cplx<T> (&y)[RPT], T& gr, T& gi) {
+__device__ __forceinline__ void dot_above(const cplx<T> (&x)[RPT], const cplx<T> (&y)[RPT], int ka, T& gr, T& gi) {
+    if constexpr (K < RPT - 1) {
+        if (K < ka) {
+            gr = fma(x[K].re, y[K].re, gr);
+            gr = fma(x[K].im, y[K].im, gr);
+            gi = fma(x[K].re, y[K].im, gi);
+            gi = fma(-x[K].im, y[K].re, gi);
+            dot_above<T, RPT, K + 1>(x, y, ka, gr, gi);
+        }
+    }
+}
+
+template <typename T, int RPT>
+__device__ __forceinline__ void dot_rows(const cplx<T> (&x)[RPT], const cplx<T> (&y)[RPT], int ka, T& gr, T& gi) {
+    constexpr int K0 = kMinSliceGroups(RPT);
 #pragma unroll
-    for (int k = 0; k < K; ++k) {
+    for (int k = 0; k < K0; ++k) {
         gr = fma(x[k].re, y[k].re, gr);
         gr = fma(x[k].im, y[k].im, gr);
         gi = fma(x[k].re, y[k].im, gi);
         gi = fma(-x[k].im, y[k].re, gi);
     }
-}
-
-template <typename T, int RPT, int... K>
-__device__ __forceinline__ void dot_rows(const cplx<T> (&x)[RPT], const cplx<T> (&y)[RPT], int ka, T& gr, T& gi,
-                                         std::integer_sequence<int, K...>) {
-    ((ka == K + 1 ? (dot_first<T, RPT, K + 1>(x, y, gr, gi), 0) : 0), ...);
+    dot_above<T, RPT, K0>(x, y, ka, gr, gi);
 }
 
 template <typename T, int RPT, int K>
-__device__ __forceinline__ T norm_first(const cplx<T> (&x)[RPT]) {
-    T acc = 0;
-#pragma unroll
-    for (int k = 0; k < K; ++k) acc += x[k].re * x[k].re + x[k].im * x[k].im;
-    return acc;
+__device__ __forceinline__ void norm_above(const cplx<T> (&x)[RPT], int ka, T& acc) {
+    if constexpr (K < RPT - 1) {
+        if (K < ka) {
+            acc += x[K].re * x[K].re + x[K].im * x[K].im;
+            norm_above<T, RPT, K + 1>(x, ka, acc);
+        }
+    }
 }
 
-template <typename T, int RPT, int... K>
-__device__ __forceinline__ T norm_rows(const cplx<T> (&x)[RPT], int ka, std::integer_sequence<int, K...>) {
+template <typename T, int RPT>
+__device__ __forceinline__ T norm_rows(const cplx<T> (&x)[RPT], int ka) {
+    constexpr int K0 = kMinSliceGroups(RPT);
     T acc = 0;
-    ((ka == K + 1 ? (acc = norm_first<T, RPT, K + 1>(x), 0) : 0), ...);
+#pragma unroll
+    for (int k = 0; k < K0; ++k) acc += x[k].re * x[k].re + x[k].im * x[k].im;
+    norm_above<T, RPT, K0>(x, ka, acc);
     return acc;
 }
 
@@ -199,7 +215,7 @@ __device__ __forceinline__ T norm_rows(const cplx<T> (&x)[RPT], int ka, std::int
 // in the element type, returned in FP64).
 template <typename T, int PG, int RPT>
 __device__ __forceinline__ double pnorm2(const cplx<T> (&x)[RPT], int ka) {
-    const T acc = norm_rows<T, RPT>(x, ka, std::make_integer_sequence<int, RPT - 1>{});
+    const T acc = norm_rows<T, RPT>(x, ka);
     return (double)group_sum<PG>(acc);
 }
 
@@ -214,27 +230,23 @@ __device__ __forceinline__ double coh_load_f64(const double* src) {
                                                              __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
 }
 
-// The part of a slice's squared Frobenius norm (slice rows) held by the
-// block pair in LDS (widths w0 and w1): per column slot g the squared norms
-// of the two blocks' columns g, added over g in order.  Every thread returns
-// the same value.  The Jacobi variants add the parts of a slice's block
-// pairs of round 0 in pair order, so all of them derive the same rounding
-// floor bit for bit.  Column slots past a block's width are not counted
-// (they may hold an earlier block's column); with ZERO_PAST_WIDTH the caller
-// guarantees that they hold zeros, and every slot is summed (adding an
-// exact 0, so the value is the same).  scratch: BW doubles of LDS.
-template <typename T, int PG, int RPT, int BW, bool ZERO_PAST_WIDTH = false>
-__device__ __forceinline__ double pair_fro_part(const cplx<T>* blk0, const cplx<T>* blk1, int w0, int w1, int ldc,
-                                                int ka, double* scratch) {
+// The part of a slice's squared Frobenius norm (slice rows) held by a
+// workgroup's block pair (widths w0 and w1; block 0 in registers, one column
+// per pair group, block 1 in LDS): per column slot g the squared norms of the
+// two blocks' columns g, added over g in order.  Every thread returns the
+// same value.  The Jacobi variants add the parts of a slice's block pairs of
+// round 0 in pair order, so all of them derive the same rounding floor bit
+// for bit.  Slots past a block's width are not counted (they may hold an
+// earlier block's column).  scratch: BW doubles of LDS.
+template <typename T, int PG, int RPT, int BW>
+__device__ __forceinline__ double pair_fro_part(const cplx<T> (&x)[RPT], const cplx<T>* blk1, int w0, int w1,
+                                                int ldc, int ka, double* scratch) {
     const int g = threadIdx.x / PG, l = threadIdx.x - g * PG;
-    cplx<T> c0[RPT], c1[RPT];
+    cplx<T> c1[RPT];
 #pragma unroll
-    for (int k = 0; k < RPT; ++k) {
-        c0[k] = blk0[g * ldc + l + PG * k];
-        c1[k] = blk1[g * ldc + l + PG * k];
-    }
-    const double n0 = pnorm2<T, PG, RPT>(c0, ka), n1 = pnorm2<T, PG, RPT>(c1, ka);
-    const double part = ZERO_PAST_WIDTH ? n0 + n1 : (g < w0 ? n0 : 0.0) + (g < w1 ? n1 : 0.0);
+    for (int k = 0; k < RPT; ++k) c1[k] = blk1[g * ldc + l + PG * k];
+    const double n0 = pnorm2<T, PG, RPT>(x, ka), n1 = pnorm2<T, PG, RPT>(c1, ka);
+    const double part = (g < w0 ? n0 : 0.0) + (g < w1 ? n1 : 0.0);
     if (l == 0) scratch[g] = part;
     __syncthreads();
     double sum = 0.0;
@@ -258,7 +270,7 @@ __device__ __forceinline__ unsigned ppair(cplx<T> (&x)[RPT], cplx<T>* y_lds, dou
 #pragma unroll
     for (int k = 0; k < RPT; ++k) y[k] = y_lds[l + PG * k];
     T gr = 0, gi = 0;
-    dot_rows<T, RPT>(x, y, ka, gr, gi, std::make_integer_sequence<int, RPT - 1>{});
+    dot_rows<T, RPT>(x, y, ka, gr, gi);
     group_sum2<PG>(gr, gi);
     const double dgr = (double)gr, dgi = (double)gi;
     const PRot rt = prot<T>(al, be, dgr, dgi, tol);
@@ -297,187 +309,272 @@ __device__ __forceinline__ void ring_wait(const int* cnt, int value) {
         if (__hip_atomic_load(cnt, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) >= value) return;
 }
 
-// LDS column of a block: slice rows 0..m-1 at 0..m-1, V rows at mp..mp+n-1
-// (mp = m rounded up to PG), zeros elsewhere.  The NT threads split into
-// BW column teams of NT / BW threads; a team copies one column, striding
-// over its rows, eight independent loads in flight per thread (addresses
-// clamped in range, so loads and stores need no branches), with no integer
-// division.
-// Complex values move as two-element vectors: a struct copy through a
-// generic pointer can be lowered through a stack temporary.
-template <typename T>
-using vec2 = T __attribute__((ext_vector_type(2)));
+// Waves per SIMD to compile a kernel of BW pair groups of PG lanes for: as
+// many workgroups as the LDS of a CU (160 KB) holds blocks, up to four waves
+// (128 registers a lane, enough for the FP32 columns and the narrower FP64
+// ones; wider FP64 columns fill the LDS alone).
+template <typename T, int PG, int BW, int RPT>
+constexpr int jacobi_waves_per_simd() {
+    constexpr int lds = BW * (PG * RPT + 1) * 2 * (int)sizeof(T) + 1024;
+    constexpr int per_cu = 160 * 1024 / lds, waves = per_cu * BW * PG / 256;
+    return waves < 1 ? 1 : (waves > 4 ? 4 : waves);
+}
 
-template <typename T, int NT, int BW>
-__device__ __forceinline__ void pcol_in(const cplx<T>* src_c, int len, cplx<T>* dst_c) {
-    constexpr int TT = NT / BW;
-    const vec2<T>* src = reinterpret_cast<const vec2<T>*>(src_c);
-    vec2<T>* dst = reinterpret_cast<vec2<T>*>(dst_c);
-    const int t = threadIdx.x % TT;
-    for (int base = t; base < len; base += 8 * TT) {
-#define TSVD_LD(u) const vec2<T> v##u = src[min(base + (u) * TT, len - 1)]
-        TSVD_LD(0); TSVD_LD(1); TSVD_LD(2); TSVD_LD(3); TSVD_LD(4); TSVD_LD(5); TSVD_LD(6); TSVD_LD(7);
-#undef TSVD_LD
-        // rows past the end rewrite the last row with its own value: no branches
-#define TSVD_ST(u) dst[min(base + (u) * TT, len - 1)] = v##u
-        TSVD_ST(0); TSVD_ST(1); TSVD_ST(2); TSVD_ST(3); TSVD_ST(4); TSVD_ST(5); TSVD_ST(6); TSVD_ST(7);
-#undef TSVD_ST
+// One round of the block tournament on one block pair of a slice.  Block 0
+// lives in registers (pair group g holds its column g in x for as long as the
+// block stays with the workgroup), block 1 in LDS, so a pair of blocks takes
+// half the LDS it would with both resident there and two workgroups share a
+// CU for slices up to 19 row groups in FP32 (9 in FP64).
+//
+// First round of a sweep (self_phase): the internal pairs of both blocks by
+// halving -- the cross pairs of a block's two halves, then of the halves of
+// each half, down to adjacent pairs: BW - 1 steps, every pair once.  The
+// groups below BW / 2 work on block 0, the others on block 1; at level k a
+// group keeps its column of the first half of its subproblem in x and meets
+// the k columns of the second half, which sit in the LDS slots of the
+// subproblem's groups.  Between levels the groups of a subproblem's second
+// half exchange their column with the slot that starts their own subproblem
+// (a group reads and writes one slot, so only barriers separate the levels),
+// and after the last level the exchanges are undone in reverse order.
+//
+// Then every cross pair: at step st group g meets column g + st of block 1,
+// which group g + 1 met at step st - 1.
+//
+// Norms are exact at the start of the round (and of every level) and tracked
+// through it.  Each level and the cross steps run wave to wave: a wave waits
+// only for the wave whose previous step wrote the column it takes next
+// (wait(count, value), the counts in wsteps never reset: steps holds the
+// number every wave has passed).  Returns the rotations applied (per thread:
+// every lane of a pair group counts its group's) and adds those that force
+// another sweep to nbig.
+template <typename T, int PG, int RPT>
+__device__ __forceinline__ void swap_slot(cplx<T> (&x)[RPT], cplx<T>* slot, int l) {
+    cplx<T> y[RPT];
+#pragma unroll
+    for (int r = 0; r < RPT; ++r) y[r] = slot[l + PG * r];
+#pragma unroll
+    for (int r = 0; r < RPT; ++r) {
+        slot[l + PG * r] = x[r];
+        x[r] = y[r];
     }
 }
 
-template <typename T, int NT, int BW>
-__device__ __forceinline__ void pcol_out(const cplx<T>* src_c, int len, cplx<T>* dst_c) {
-    constexpr int TT = NT / BW;
-    const vec2<T>* src = reinterpret_cast<const vec2<T>*>(src_c);
-    vec2<T>* dst = reinterpret_cast<vec2<T>*>(dst_c);
-    for (int r = threadIdx.x % TT; r < len; r += TT) dst[r] = src[r];
+template <typename T, int PG, int BW, int RPT, typename Wait>
+__device__ __forceinline__ unsigned pair_round(cplx<T> (&x)[RPT], cplx<T>* blk1, int wi, int wj, bool self_phase,
+                                               int ka, int ldc, double tol, double floor2, double* jnorm,
+                                               int* wsteps, int& steps, unsigned& nbig, Wait&& wait) {
+    constexpr int NW = BW * PG / 64;
+    const int g = threadIdx.x / PG, l = threadIdx.x - g * PG;
+    const int wave = threadIdx.x >> 6;
+    unsigned nrot = 0;
+    if (self_phase) {
+        const bool second = g >= BW / 2;
+        const int gi = second ? g - BW / 2 : g;
+        cplx<T>* const base = blk1 + (second ? (BW / 2) * ldc : 0);   // the block's second-half slots
+        double* const jn = jnorm + (second ? BW / 2 : 0);
+        const int w = second ? wj : wi;
+        // block 0's upper half to LDS, block 1's lower half to registers
+        if (second) swap_slot<T, PG, RPT>(x, blk1 + gi * ldc, l);
+        __syncthreads();
+        for (int k = BW / 2; k >= 1; k /= 2) {
+            const int sp = gi / k, q = gi - sp * k;
+            const int xcol = 2 * k * sp + q, ycol0 = 2 * k * sp + k;
+            // a subproblem of k groups spans k / 2 consecutive waves (one if k <= 2)
+            const int span = k * PG >= 128 ? k * PG / 64 : 1, wl = wave % span;
+            const int wnext = wave - wl + (wl + 1) % span;
+            double ax = pnorm2<T, PG, RPT>(x, ka);
+            {
+                cplx<T> yr[RPT];
+#pragma unroll
+                for (int r = 0; r < RPT; ++r) yr[r] = base[gi * ldc + l + PG * r];
+                const double bq = pnorm2<T, PG, RPT>(yr, ka);
+                if (l == 0) jn[gi] = bq;
+            }
+            __syncthreads();
+            for (int st = 0; st < k; ++st) {
+                if (st > 0) wait(wsteps + wnext, steps + st);
+                const int yo = (q + st) & (k - 1), ys = k * sp + yo;
+                if (xcol < w && ycol0 + yo < w) {
+                    double be = jn[ys];
+                    if (const unsigned code = ppair<T, PG, RPT>(x, base + ys * ldc, ax, be, ka, l, tol, floor2)) {
+                        ++nrot;
+                        nbig += code >> 1;
+                        if (l == 0) jn[ys] = be;
+                    }
+                }
+                ring_publish(wsteps + wave, steps + st + 1);
+            }
+            steps += k;
+            __syncthreads();
+            if (k > 1) {
+                if (q >= k / 2) swap_slot<T, PG, RPT>(x, base + (k * sp + q - k / 2) * ldc, l);
+                __syncthreads();
+            }
+        }
+        for (int k = 2; k <= BW / 2; k *= 2) {
+            const int sp = gi / k, q = gi - sp * k;
+            if (q >= k / 2) swap_slot<T, PG, RPT>(x, base + (k * sp + q - k / 2) * ldc, l);
+            __syncthreads();
+        }
+        if (second) swap_slot<T, PG, RPT>(x, blk1 + gi * ldc, l);
+        __syncthreads();
+    }
+    const int wave_next = (wave + 1) % NW;
+    double al = pnorm2<T, PG, RPT>(x, ka);
+    {
+        cplx<T> yj[RPT];
+#pragma unroll
+        for (int k = 0; k < RPT; ++k) yj[k] = blk1[g * ldc + l + PG * k];
+        const double bj = pnorm2<T, PG, RPT>(yj, ka);
+        if (l == 0) jnorm[g] = bj;
+    }
+    __syncthreads();
+    for (int st = 0; st < BW; ++st) {
+        if (st > 0) wait(wsteps + wave_next, steps + st);
+        const int jc = (g + st) & (BW - 1);
+        if (g < wi && jc < wj) {
+            double be = jnorm[jc];
+            if (const unsigned code = ppair<T, PG, RPT>(x, blk1 + jc * ldc, al, be, ka, l, tol, floor2)) {
+                ++nrot;
+                nbig += code >> 1;
+                if (l == 0) jnorm[jc] = be;
+            }
+        }
+        ring_publish(wsteps + wave, steps + st + 1);
+    }
+    steps += BW;
+    __syncthreads();
+    return nrot;
 }
 
-// Device-coherent copies: relaxed agent-scope atomic loads and stores, which
-// the hardware serves at the device's coherence point (never from a stale
-// L2 line of another XCD).  Used by workgroups that exchange blocks through
-// global memory inside one launch, so that no L2 write-back or invalidation
-// is needed around the exchange.
+// Stacked column of a block: slice rows 0..m-1 at 0..m-1, V rows at
+// mp..mp+n-1 (mp = m rounded up to PG), zeros elsewhere; pair group c holds or
+// moves column c, lane t the rows t + PG r, so a row group is either slice
+// rows or V rows.
+//
+// Columns move through buffer resources of the slice's two matrices: an
+// address per lane takes one register, and padding rows and columns past the
+// block's width get an address past the end, where a load returns zeros and a
+// store does nothing, so there are no branches and every load of an exchange
+// is in flight at once.  COH: device-coherent transfers (sc1, what an
+// agent-scope relaxed atomic uses), served at the device's coherence point
+// and never from a stale L2 line of another XCD, so workgroups that exchange
+// blocks through global memory inside one launch need no L2 write-back or
+// invalidation around the exchange.
 template <typename T>
-__device__ __forceinline__ void coh_copy_in(const cplx<T>* src, cplx<T>* dst);
+struct SliceView {
+    __amdgpu_buffer_rsrc_t A;   // m x n, column-major
+    __amdgpu_buffer_rsrc_t V;   // n x n, column-major
+    int m, n, nb, ka, ldc;
+};
 
-template <>
-__device__ __forceinline__ void coh_copy_in<float>(const cplx<float>* src, cplx<float>* dst) {
-    const unsigned long long u = __hip_atomic_load(reinterpret_cast<const unsigned long long*>(src),
-                                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    *reinterpret_cast<unsigned long long*>(dst) = u;
-}
-
-template <>
-__device__ __forceinline__ void coh_copy_in<double>(const cplx<double>* src, cplx<double>* dst) {
-    const unsigned long long* s = reinterpret_cast<const unsigned long long*>(src);
-    unsigned long long* d = reinterpret_cast<unsigned long long*>(dst);
-    const unsigned long long a = __hip_atomic_load(s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const unsigned long long b = __hip_atomic_load(s + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    d[0] = a;
-    d[1] = b;
+template <typename T>
+__device__ __forceinline__ SliceView<T> slice_view(cplx<T>* A, cplx<T>* V, int m, int n, int nb, int ka, int ldc) {
+    constexpr int kRaw = 0x00027000;   // raw buffer, 32-bit data format
+    return {__builtin_amdgcn_make_buffer_rsrc(A, 0, m * n * (int)sizeof(cplx<T>), kRaw),
+            __builtin_amdgcn_make_buffer_rsrc(V, 0, n * n * (int)sizeof(cplx<T>), kRaw), m, n, nb, ka, ldc};
 }
 
 template <typename T>
-__device__ __forceinline__ void coh_copy_out(const cplx<T>* src, cplx<T>* dst);
-
+struct BufWord;
 template <>
-__device__ __forceinline__ void coh_copy_out<float>(const cplx<float>* src, cplx<float>* dst) {
-    __hip_atomic_store(reinterpret_cast<unsigned long long*>(dst), *reinterpret_cast<const unsigned long long*>(src),
-                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
+struct BufWord<float> {
+    using type = unsigned __attribute__((ext_vector_type(2)));
+    template <int AUX>
+    static __device__ __forceinline__ type load(__amdgpu_buffer_rsrc_t b, int off) {
+        return __builtin_amdgcn_raw_buffer_load_b64(b, off, 0, AUX);
+    }
+    template <int AUX>
+    static __device__ __forceinline__ void store(type v, __amdgpu_buffer_rsrc_t b, int off) {
+        __builtin_amdgcn_raw_buffer_store_b64(v, b, off, 0, AUX);
+    }
+};
 template <>
-__device__ __forceinline__ void coh_copy_out<double>(const cplx<double>* src, cplx<double>* dst) {
-    const unsigned long long* s = reinterpret_cast<const unsigned long long*>(src);
-    unsigned long long* d = reinterpret_cast<unsigned long long*>(dst);
-    __hip_atomic_store(d, s[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(d + 1, s[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
+struct BufWord<double> {
+    using type = unsigned __attribute__((ext_vector_type(4)));
+    template <int AUX>
+    static __device__ __forceinline__ type load(__amdgpu_buffer_rsrc_t b, int off) {
+        return __builtin_amdgcn_raw_buffer_load_b128(b, off, 0, AUX);
+    }
+    template <int AUX>
+    static __device__ __forceinline__ void store(type v, __amdgpu_buffer_rsrc_t b, int off) {
+        __builtin_amdgcn_raw_buffer_store_b128(v, b, off, 0, AUX);
+    }
+};
 
+// Byte offset of row `row` (of `len`) of a column that starts at element
+// `start` (-1: no column); past the end of every slice when it does not exist.
 template <typename T>
-__device__ __forceinline__ cplx<T> coh_load(const cplx<T>* src) {
-    cplx<T> v;
-    coh_copy_in<T>(src, &v);
+__device__ __forceinline__ int elem_offset(int start, int row, int len) {
+    return start >= 0 && row < len ? (start + row) * (int)sizeof(cplx<T>) : -16;
+}
+
+// The column of block blk that pair group c takes, -1 past the block's width.
+template <typename T>
+__device__ __forceinline__ int block_col(const SliceView<T>& s, int blk, int c) {
+    const int c0 = pblk_start(blk, s.n, s.nb);
+    return c < pblk_start(blk + 1, s.n, s.nb) - c0 ? c0 + c : -1;
+}
+
+// The value, of unknown origin to the compiler: keeps the row tests and
+// offsets of a transfer (two per row group) from being computed once and held
+// in registers through the sweeps.
+__device__ __forceinline__ int opaque(int v) {
+    asm volatile("" : "+v"(v));
     return v;
 }
 
-// Eight coherent loads in flight per thread (addresses clamped in range;
-// rows past the end rewrite the last row with its own value).
-template <typename T, int NT, int BW>
-__device__ __forceinline__ void ccol_in(const cplx<T>* src, int len, cplx<T>* dst_c) {
-    constexpr int TT = NT / BW;
-    vec2<T>* dst = reinterpret_cast<vec2<T>*>(dst_c);
-    const int t = threadIdx.x % TT;
-    for (int base = t; base < len; base += 8 * TT) {
-#define TSVD_LD(u) const cplx<T> v##u = coh_load<T>(src + min(base + (u) * TT, len - 1))
-        TSVD_LD(0); TSVD_LD(1); TSVD_LD(2); TSVD_LD(3); TSVD_LD(4); TSVD_LD(5); TSVD_LD(6); TSVD_LD(7);
-#undef TSVD_LD
-#define TSVD_ST(u) dst[min(base + (u) * TT, len - 1)] = vec2<T>{v##u.re, v##u.im}
-        TSVD_ST(0); TSVD_ST(1); TSVD_ST(2); TSVD_ST(3); TSVD_ST(4); TSVD_ST(5); TSVD_ST(6); TSVD_ST(7);
-#undef TSVD_ST
-    }
-}
-
-template <typename T, int NT, int BW>
-__device__ __forceinline__ void ccol_out(const cplx<T>* src, int len, cplx<T>* dst) {
-    constexpr int TT = NT / BW;
-    for (int r = threadIdx.x % TT; r < len; r += TT) coh_copy_out<T>(src + r, dst + r);
-}
-
-// Block blk of a slice (A: m x n, V: n x n, column-major) to / from LDS;
-// COH selects the device-coherent copies.
-template <typename T, int NT, int BW, bool COH = false>
-__device__ __forceinline__ void load_block(const cplx<T>* A, const cplx<T>* V, int m, int n, int nb, int blk,
-                                           int mp, int ldc, cplx<T>* lds) {
-    const int c0 = pblk_start(blk, n, nb), w = pblk_start(blk + 1, n, nb) - c0;
-    const int c = threadIdx.x / (NT / BW);
-    if (c < w) {
-        if (COH) {
-            ccol_in<T, NT, BW>(A + (int64_t)(c0 + c) * m, m, lds + c * ldc);
-            ccol_in<T, NT, BW>(V + (int64_t)(c0 + c) * n, n, lds + c * ldc + mp);
-        } else {
-            pcol_in<T, NT, BW>(A + (int64_t)(c0 + c) * m, m, lds + c * ldc);
-            pcol_in<T, NT, BW>(V + (int64_t)(c0 + c) * n, n, lds + c * ldc + mp);
-        }
-    }
-}
-
-// Block blk into LDS with all of a lane's loads in flight before its first
-// LDS store (one memory round trip per block): pair group c (PG lanes) takes
-// column c, lane t the stacked rows t + PG r (slice rows below m, V rows
-// from mp), one address and one predicate per row.  The FP32 block-pair
-// kernel takes its incoming blocks with it between rounds (the 64-problem
-// batch 3% faster than with the per-segment copies); in FP64 the unrolled
-// rows take too many registers, and in the one-workgroup-per-slice kernel
-// it brought no clear gain for many more scalar spills.
 template <typename T, int PG, int RPT, bool COH>
-__device__ __forceinline__ void load_block_rows(const cplx<T>* A, const cplx<T>* V, int m, int n, int nb, int blk,
-                                                int mp, int ldc, cplx<T>* lds) {
+__device__ __forceinline__ void load_col(const SliceView<T>& s, int blk, cplx<T> (&x)[RPT]) {
+    const int c = threadIdx.x / PG, t = opaque(threadIdx.x - c * PG);
+    const int ka = __builtin_amdgcn_readfirstlane(opaque(s.ka));
+    const int col = block_col(s, blk, c);
+    const int sa = col < 0 ? -1 : col * s.m, sv = col < 0 ? -1 : col * s.n;
+#pragma unroll
+    for (int r = 0; r < RPT; ++r)
+        x[r] = __builtin_bit_cast(
+            cplx<T>, r < ka ? BufWord<T>::template load<COH ? 16 : 0>(s.A, elem_offset<T>(sa, t + PG * r, s.m))
+                              : BufWord<T>::template load<COH ? 16 : 0>(
+                                    s.V, elem_offset<T>(sv, t + PG * (r - ka), s.n)));
+}
+
+template <typename T, int PG, int RPT, bool COH>
+__device__ __forceinline__ void store_col(const SliceView<T>& s, int blk, const cplx<T> (&x)[RPT]) {
+    const int c = threadIdx.x / PG, t = opaque(threadIdx.x - c * PG);
+    const int ka = __builtin_amdgcn_readfirstlane(opaque(s.ka));
+    const int col = block_col(s, blk, c);
+    const int sa = col < 0 ? -1 : col * s.m, sv = col < 0 ? -1 : col * s.n;
+#pragma unroll
+    for (int r = 0; r < RPT; ++r) {
+        const auto w = __builtin_bit_cast(typename BufWord<T>::type, x[r]);
+        if (r < ka)
+            BufWord<T>::template store<COH ? 16 : 0>(w, s.A, elem_offset<T>(sa, t + PG * r, s.m));
+        else
+            BufWord<T>::template store<COH ? 16 : 0>(w, s.V, elem_offset<T>(sv, t + PG * (r - ka), s.n));
+    }
+}
+
+template <typename T, int PG, int RPT, bool COH>
+__device__ __forceinline__ void store_lds(const SliceView<T>& s, int blk, const cplx<T>* lds) {
     const int c = threadIdx.x / PG, t = threadIdx.x - c * PG;
-    const int c0 = pblk_start(blk, n, nb);
-    const int col = c < pblk_start(blk + 1, n, nb) - c0 ? c0 + c : -1;
-    cplx<T> v[RPT];
+    cplx<T> y[RPT];
 #pragma unroll
-    for (int r = 0; r < RPT; ++r) {
-        const int R = t + PG * r;
-        if (col >= 0 && (R < m || (R >= mp && R - mp < n))) {
-            const cplx<T>* p = R < m ? A + (int64_t)col * m + R : V + (int64_t)col * n + (R - mp);
-            if constexpr (COH) v[r] = coh_load<T>(p);
-            else v[r] = *p;
-        }
-    }
-#pragma unroll
-    for (int r = 0; r < RPT; ++r) {
-        const int R = t + PG * r;
-        if (col >= 0 && (R < m || (R >= mp && R - mp < n))) lds[c * ldc + R] = v[r];
-    }
+    for (int r = 0; r < RPT; ++r) y[r] = lds[c * s.ldc + t + PG * r];
+    store_col<T, PG, RPT, COH>(s, blk, y);
 }
 
-// Block blk into LDS: load_block_rows in FP32, the per-segment copies
-// (load_block) in FP64.
-template <typename T, int PG, int RPT, int BW, bool COH = false>
-__device__ __forceinline__ void load_block_any(const cplx<T>* A, const cplx<T>* V, int m, int n, int nb, int blk,
-                                               int mp, int ldc, cplx<T>* lds) {
-    if constexpr (sizeof(T) == 4)
-        load_block_rows<T, PG, RPT, COH>(A, V, m, n, nb, blk, mp, ldc, lds);
-    else
-        load_block<T, BW * PG, BW, COH>(A, V, m, n, nb, blk, mp, ldc, lds);
-}
-
-template <typename T, int NT, int BW, bool COH = false>
-__device__ __forceinline__ void store_block(cplx<T>* A, cplx<T>* V, int m, int n, int nb, int blk, int mp,
-                                            int ldc, const cplx<T>* lds) {
-    const int c0 = pblk_start(blk, n, nb), w = pblk_start(blk + 1, n, nb) - c0;
-    const int c = threadIdx.x / (NT / BW);
-    if (c < w) {
-        if (COH) {
-            ccol_out<T, NT, BW>(lds + c * ldc, m, A + (int64_t)(c0 + c) * m);
-            ccol_out<T, NT, BW>(lds + c * ldc + mp, n, V + (int64_t)(c0 + c) * n);
-        } else {
-            pcol_out<T, NT, BW>(lds + c * ldc, m, A + (int64_t)(c0 + c) * m);
-            pcol_out<T, NT, BW>(lds + c * ldc + mp, n, V + (int64_t)(c0 + c) * n);
-        }
+// The blocks blk0 (into registers) and blk1 (into LDS), -1: keep; all loads of
+// both in flight together.
+template <typename T, int PG, int RPT, bool COH>
+__device__ __forceinline__ void load_pair(const SliceView<T>& s, int blk0, cplx<T> (&x)[RPT], int blk1,
+                                          cplx<T>* lds) {
+    const int c = threadIdx.x / PG, t = threadIdx.x - c * PG;
+    cplx<T> y[RPT];
+    if (blk1 >= 0) load_col<T, PG, RPT, COH>(s, blk1, y);
+    if (blk0 >= 0) load_col<T, PG, RPT, COH>(s, blk0, x);
+    if (blk1 >= 0) {
+#pragma unroll
+        for (int r = 0; r < RPT; ++r) lds[c * s.ldc + t + PG * r] = y[r];
     }
 }
 

@@ -63,96 +63,6 @@ using namespace jac;
 
 constexpr int PBW = 16;   // columns per block = pairs per step
 
-template <typename T, int NT>
-__device__ void pload_block(const JacArgs<T>& a, int s, int blk, int mp, int ldc, cplx<T>* lds) {
-    load_block<T, NT, PBW, true>(a.A + (int64_t)s * a.n * a.m, a.V + (int64_t)s * a.n * a.n, a.m, a.n, a.nb, blk,
-                                 mp, ldc, lds);
-}
-
-// The blocks blk0 and blk1 (-1: none) into LDS.  Up to 10 rows per lane
-// every load is in flight before the first LDS store, one memory round trip
-// for both blocks, slice and V rows, instead of one per block and row
-// segment, with one address and one predicate per row (a select between
-// the slice and the V part): +2.9% iterations/s in the FP32 form and +4.5%
-// in FP64 on the video shape (9 rows per lane).  Wider columns keep the
-// earlier loaders, which hold fewer registers: FP64 the combined loader with
-// a branch per row segment, FP32 the per-block loads (the combined loaders
-// double the wide FP32 kernels' scalar register spills).  Reading both
-// blocks from LDS before the first store of an exchange was 5% slower, so
-// the stores stay per block.  Thread team c (PG lanes) takes column c of
-// each block, lane t the stacked rows t + PG r: slice rows below m, V rows
-// from mp (the padding rows between stay zero).
-template <typename T, int PG, int RPT>
-__device__ __forceinline__ void pload_pair(const JacArgs<T>& a, int s, int mp, int ldc, int blk0, cplx<T>* lds0,
-                                           int blk1, cplx<T>* lds1) {
-    if constexpr (sizeof(T) == 4 && RPT > 10) {
-        constexpr int NT = PBW * PG;
-        if (blk0 >= 0) pload_block<T, NT>(a, s, blk0, mp, ldc, lds0);
-        if (blk1 >= 0) pload_block<T, NT>(a, s, blk1, mp, ldc, lds1);
-        return;
-    }
-    const int c = threadIdx.x / PG, t = threadIdx.x - c * PG;
-    const cplx<T>* const A = a.A + (int64_t)s * a.n * a.m;
-    const cplx<T>* const V = a.V + (int64_t)s * a.n * a.n;
-    const int m = a.m, n = a.n;
-    auto col = [&](int blk) {
-        if (blk < 0) return -1;
-        const int c0 = pblk_start(blk, n, a.nb);
-        return c < pblk_start(blk + 1, n, a.nb) - c0 ? c0 + c : -1;
-    };
-    const int col0 = col(blk0), col1 = col(blk1);
-    if constexpr (RPT <= 10) {
-        auto addr = [&](int cl, int R) {
-            return R < m ? A + (int64_t)cl * m + R : V + (int64_t)cl * n + (R - mp);
-        };
-        auto live = [&](int cl, int R) { return cl >= 0 && (R < m || (R >= mp && R - mp < n)); };
-        cplx<T> v0[RPT], v1[RPT];
-#pragma unroll
-        for (int r = 0; r < RPT; ++r) {
-            const int R = t + PG * r;
-            if (live(col0, R)) v0[r] = coh_load<T>(addr(col0, R));
-            if (live(col1, R)) v1[r] = coh_load<T>(addr(col1, R));
-        }
-#pragma unroll
-        for (int r = 0; r < RPT; ++r) {
-            const int R = t + PG * r;
-            if (live(col0, R)) lds0[c * ldc + R] = v0[r];
-            if (live(col1, R)) lds1[c * ldc + R] = v1[r];
-        }
-        return;
-    }
-    cplx<T> v0[RPT], v1[RPT];
-#pragma unroll
-    for (int r = 0; r < RPT; ++r) {
-        const int R = t + PG * r;
-        if (col0 >= 0) {
-            if (R < m)
-                v0[r] = coh_load<T>(A + (int64_t)col0 * m + R);
-            else if (R >= mp && R - mp < n)
-                v0[r] = coh_load<T>(V + (int64_t)col0 * n + (R - mp));
-        }
-        if (col1 >= 0) {
-            if (R < m)
-                v1[r] = coh_load<T>(A + (int64_t)col1 * m + R);
-            else if (R >= mp && R - mp < n)
-                v1[r] = coh_load<T>(V + (int64_t)col1 * n + (R - mp));
-        }
-    }
-#pragma unroll
-    for (int r = 0; r < RPT; ++r) {
-        const int R = t + PG * r;
-        const bool row = R < m || (R >= mp && R - mp < n);
-        if (col0 >= 0 && row) lds0[c * ldc + R] = v0[r];
-        if (col1 >= 0 && row) lds1[c * ldc + R] = v1[r];
-    }
-}
-
-template <typename T, int NT>
-__device__ void pstore_block(const JacArgs<T>& a, int s, int blk, int mp, int ldc, const cplx<T>* lds) {
-    store_block<T, NT, PBW, true>(a.A + (int64_t)s * a.n * a.m, a.V + (int64_t)s * a.n * a.n, a.m, a.n, a.nb, blk,
-                                  mp, ldc, lds);
-}
-
 // Slice barrier: returns false if the bounded wait ran out.
 //
 // The blocks travel through global memory with device-coherent (relaxed
@@ -210,10 +120,6 @@ __device__ bool wait_flag(int* flag, int value, int* err, int spin_limit) {
 // and sets the error word to 2, which fails the call (the block data can no
 // longer be trusted); it checks the error word every 1024 polls, so after
 // such a fault no wait spins to its cap again.
-__device__ __forceinline__ void lds_publish(int* cnt, int value) {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    if ((threadIdx.x & 63) == 0) __hip_atomic_store(cnt, value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
 
 // Polls back to back (a sleep between polls cost 0.7% of the iteration);
 // 2^18 LDS polls are milliseconds, far beyond any step of a workgroup's own
@@ -245,7 +151,6 @@ __global__ __launch_bounds__(PBW * PG) void jacobi_persistent_kernel(JacArgs<T> 
     __shared__ int stop;
     __shared__ int ok_flag;
     __shared__ double jnorm[PBW];
-    __shared__ double inorm[2 * PBW];   // internal phase: tracked norms of both blocks' columns
     __shared__ int wsteps[NT / 64];   // pair steps finished per wave, over the whole launch
     __shared__ int role;
     if (a.ctrl && a.ctrl->done) return;
@@ -261,26 +166,25 @@ __global__ __launch_bounds__(PBW * PG) void jacobi_persistent_kernel(JacArgs<T> 
     const int s = rl / G, wg = rl - s * G;
     if (s >= a.h) return;
     const int ka = (a.m + PG - 1) / PG;   // row groups holding slice rows
-    const int mp = ka * PG;
     // column stride: the padded stacked column plus one element, so the pair
     // groups of a wavefront read different LDS banks
     const int ldc = PG * RPT + 1;
-    cplx<T>* const blk0 = reinterpret_cast<cplx<T>*>(smem);
-    cplx<T>* const blk1 = blk0 + (size_t)PBW * ldc;
+    const SliceView<T> sv =
+        slice_view(a.A + (int64_t)s * a.n * a.m, a.V + (int64_t)s * a.n * a.n, a.m, a.n, a.nb, ka, ldc);
+    cplx<T>* const blk1 = reinterpret_cast<cplx<T>*>(smem);
+    cplx<T> x[RPT];
     const int pos0 = wg, pos1 = a.nb - 1 - wg;
-    const int g = threadIdx.x / PG, l = threadIdx.x - g * PG;
+    const int l = threadIdx.x % PG;
     const double tol = (double)a.tol;
     int* counter = p.pbar + s;
     int arrivals = 0;
+    auto width = [&](int b) { return pblk_start(b + 1, a.n, a.nb) - pblk_start(b, a.n, a.nb); };
+    auto wait = [&](const int* cnt, int value) { lds_wait(cnt, value, err); };
 
-    // zero both blocks once: padding rows stay zero under every rotation
-    for (int idx = threadIdx.x; idx < 2 * PBW * ldc; idx += NT) blk0[idx] = cplx<T>{(T)0, (T)0};
-    const int wave = threadIdx.x >> 6, wave_next = (wave + 1) % (NT / 64);
-    if ((threadIdx.x & 63) == 0) wsteps[wave] = 0;
-    int steps = 0;   // cross steps finished by every wave before the current round
-    __syncthreads();
+    if ((threadIdx.x & 63) == 0) wsteps[threadIdx.x >> 6] = 0;
+    int steps = 0;   // pair steps finished by every wave before the current round
     int player0 = ppos_player(pos0, 0, a.nb), player1 = ppos_player(pos1, 0, a.nb);
-    pload_pair<T, PG, RPT>(a, s, mp, ldc, player0, blk0, player1, blk1);
+    load_pair<T, PG, RPT, true>(sv, player0, x, player1, blk1);
     if (wg == 0 && threadIdx.x == 0) a.sweeps[s] = 0;
     __syncthreads();
 
@@ -293,8 +197,8 @@ __global__ __launch_bounds__(PBW * PG) void jacobi_persistent_kernel(JacArgs<T> 
     bool home0 = true, home1 = true;
     double floor2 = 0.0;   // rounding floor of rot_forces_sweep
     if (p.floor_scale > 0.0) {
-        // the slots past a block's width were zeroed before the first load
-        const double part = pair_fro_part<T, PG, RPT, PBW, true>(blk0, blk1, PBW, PBW, ldc, ka, inorm);
+        const double part =
+            pair_fro_part<T, PG, RPT, PBW>(x, blk1, width(player0), width(player1), ldc, ka, jnorm);
         if (threadIdx.x == 0) coh_store_f64(p.fro + (int64_t)s * G + wg, part);
         arrivals += G;
         if (!slice_barrier(counter, arrivals, err, p.spin_limit)) {
@@ -303,10 +207,10 @@ __global__ __launch_bounds__(PBW * PG) void jacobi_persistent_kernel(JacArgs<T> 
             if (threadIdx.x == 0) {
                 double fro2 = 0.0;
                 for (int i = 0; i < G; ++i) fro2 += coh_load_f64(p.fro + (int64_t)s * G + i);
-                inorm[0] = p.floor_scale * fro2;
+                jnorm[0] = p.floor_scale * fro2;
             }
             __syncthreads();
-            floor2 = inorm[0];
+            floor2 = jnorm[0];
             __syncthreads();
         }
     }
@@ -321,99 +225,9 @@ __global__ __launch_bounds__(PBW * PG) void jacobi_persistent_kernel(JacArgs<T> 
         }
         __syncthreads();
         unsigned nrot = 0, nbig = 0;   // rotations of the sweep; those that force another sweep
-        {
-            // Internal pairs of both resident blocks (groups 0-7 take block 0,
-            // groups 8-15 block 1) by halving: the 8 x 8 cross pairs of the
-            // block's two halves, then the 4 x 4 cross pairs within each half,
-            // then 2 x 2, then the 8 adjacent pairs -- 15 steps, every pair once.
-            // Each level runs like a cross round: a group keeps its column of
-            // the first half of its subproblem in registers and meets the k
-            // columns of the second half, norms exact at the level's start and
-            // tracked through it, and a wave waits only for the wave whose
-            // previous step wrote the column it takes next.
-            const bool second = g >= PBW / 2;
-            const int gi = second ? g - PBW / 2 : g;
-            const int pl = second ? player1 : player0;
-            cplx<T>* const base = second ? blk1 : blk0;
-            double* const jn = inorm + (second ? PBW : 0);
-            const int w = pblk_start(pl + 1, a.n, a.nb) - pblk_start(pl, a.n, a.nb);
-            const int wl = wave & 3, wbase = wave & ~3;   // waves 0-3 hold block 0, 4-7 block 1
-            for (int k = PBW / 2; k >= 1; k /= 2) {
-                const int sp = gi / k, q = gi - sp * k;
-                const int xcol = 2 * k * sp + q, ybase = 2 * k * sp + k;
-                // the wave holding group (q + 1) mod k of this subproblem
-                const int wnext = k == 8 ? wbase + ((wl + 1) & 3) : (k == 4 ? wave ^ 1 : wave);
-                cplx<T> xr[RPT];
-#pragma unroll
-                for (int r = 0; r < RPT; ++r) xr[r] = base[xcol * ldc + l + PG * r];
-                double al = pnorm2<T, PG, RPT>(xr, ka);
-                {
-                    cplx<T> yr[RPT];
-#pragma unroll
-                    for (int r = 0; r < RPT; ++r) yr[r] = base[(ybase + q) * ldc + l + PG * r];
-                    const double bq = pnorm2<T, PG, RPT>(yr, ka);
-                    if (l == 0) jn[ybase + q] = bq;
-                }
-                __syncthreads();
-                for (int st = 0; st < k; ++st) {
-                    if (st > 0) lds_wait(wsteps + wnext, steps + st, err);
-                    const int ycol = ybase + ((q + st) & (k - 1));
-                    if (xcol < w && ycol < w) {
-                        double be = jn[ycol];
-                        if (const unsigned code = ppair<T, PG, RPT>(xr, base + ycol * ldc, al, be, ka, l, tol, floor2)) {
-                            ++nrot;
-                            nbig += code >> 1;
-                            if (l == 0) jn[ycol] = be;
-                        }
-                    }
-                    lds_publish(wsteps + wave, steps + st + 1);
-                }
-                steps += k;
-                if (xcol < w) {
-#pragma unroll
-                    for (int r = 0; r < RPT; ++r) base[xcol * ldc + l + PG * r] = xr[r];
-                }
-                __syncthreads();
-            }
-        }
         for (int rd = 0; rd < a.nb - 1; ++rd) {
-            // cross pairs: column g of block 0 (registers) meets every column of block 1
-            const int wi = pblk_start(player0 + 1, a.n, a.nb) - pblk_start(player0, a.n, a.nb);
-            const int wj = pblk_start(player1 + 1, a.n, a.nb) - pblk_start(player1, a.n, a.nb);
-            cplx<T> xi[RPT];
-#pragma unroll
-            for (int k = 0; k < RPT; ++k) xi[k] = blk0[g * ldc + l + PG * k];
-            // exact squared norms at the start of the round, tracked within it
-            double al = pnorm2<T, PG, RPT>(xi, ka);
-            {
-                cplx<T> yj[RPT];
-#pragma unroll
-                for (int k = 0; k < RPT; ++k) yj[k] = blk1[g * ldc + l + PG * k];
-                const double bj = pnorm2<T, PG, RPT>(yj, ka);
-                if (l == 0) jnorm[g] = bj;
-            }
-            __syncthreads();
-            // step st: group g meets column (g + st) mod PBW of block 1, which
-            // group g + 1 met at step st - 1
-            for (int st = 0; st < PBW; ++st) {
-                if (st > 0) lds_wait(wsteps + wave_next, steps + st, err);
-                const int jc = (g + st) & (PBW - 1);
-                if (g < wi && jc < wj) {
-                    double be = jnorm[jc];
-                    if (const unsigned code = ppair<T, PG, RPT>(xi, blk1 + jc * ldc, al, be, ka, l, tol, floor2)) {
-                        ++nrot;
-                        nbig += code >> 1;
-                        if (l == 0) jnorm[jc] = be;
-                    }
-                }
-                lds_publish(wsteps + wave, steps + st + 1);
-            }
-            steps += PBW;
-            __syncthreads();
-            if (g < wi) {
-#pragma unroll
-                for (int k = 0; k < RPT; ++k) blk0[g * ldc + l + PG * k] = xi[k];
-            }
+            nrot += pair_round<T, PG, PBW, RPT>(x, blk1, width(player0), width(player1), rd == 0, ka, ldc, tol, floor2,
+                                                jnorm, wsteps, steps, nbig, wait);
             // end of the sweep: publish whether this workgroup needs another sweep
             const bool last = rd == a.nb - 2;
             if (last) {
@@ -426,9 +240,8 @@ __global__ __launch_bounds__(PBW * PG) void jacobi_persistent_kernel(JacArgs<T> 
             // the next round's players (after the last round: round 0 of the next sweep)
             const int nr = (rd + 1) % (a.nb - 1);
             const int next0 = ppos_player(pos0, nr, a.nb), next1 = ppos_player(pos1, nr, a.nb);
-            __syncthreads();
-            if (next0 != player0) pstore_block<T, NT>(a, s, player0, mp, ldc, blk0);
-            if (next1 != player1) pstore_block<T, NT>(a, s, player1, mp, ldc, blk1);
+            if (next0 != player0) store_col<T, PG, RPT, true>(sv, player0, x);
+            if (next1 != player1) store_lds<T, PG, RPT, true>(sv, player1, blk1);
             if (last) {
                 // end of the sweep: every workgroup of the slice meets, then all
                 // read the same rotation flag and stop together when it is clear
@@ -471,8 +284,7 @@ __global__ __launch_bounds__(PBW * PG) void jacobi_persistent_kernel(JacArgs<T> 
                     break;
                 }
             }
-            pload_pair<T, PG, RPT>(a, s, mp, ldc, next0 != player0 ? next0 : -1, blk0,
-                                   next1 != player1 ? next1 : -1, blk1);
+            load_pair<T, PG, RPT, true>(sv, next0 != player0 ? next0 : -1, x, next1 != player1 ? next1 : -1, blk1);
             player0 = next0;
             player1 = next1;
             __syncthreads();
@@ -480,8 +292,8 @@ __global__ __launch_bounds__(PBW * PG) void jacobi_persistent_kernel(JacArgs<T> 
         nrot_total += nrot;
     }
     __syncthreads();
-    if (home0) pstore_block<T, NT>(a, s, player0, mp, ldc, blk0);
-    if (home1) pstore_block<T, NT>(a, s, player1, mp, ldc, blk1);
+    if (home0) store_col<T, PG, RPT, true>(sv, player0, x);
+    if (home1) store_lds<T, PG, RPT, true>(sv, player1, blk1);
     if (l == 0 && nrot_total) atomicAdd(a.rotations, (unsigned long long)nrot_total);
     if (a.ctrl && swept) atomicMax(&a.ctrl->sweep_max, swept);
 }
@@ -500,7 +312,7 @@ int persist_rpt(int m, int n) {
     return -1;
 }
 
-size_t persist_lds(int rpt, int elem_bytes) { return 2 * (size_t)PBW * (kPG * rpt + 1) * 2 * elem_bytes; }
+size_t persist_lds(int rpt, int elem_bytes) { return (size_t)PBW * (kPG * rpt + 1) * 2 * elem_bytes; }
 
 template <typename T, int RPT>
 hipError_t launch_persist_t(const JacArgs<T>& a, const PersistArgs& p, size_t lds, hipStream_t st, int cus) {
