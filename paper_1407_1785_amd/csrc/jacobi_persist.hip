@@ -4,8 +4,9 @@
 // not fit this one).
 //
 // Layout.  Slice s gets G = nb/2 workgroups; workgroup p holds the blocks at
-// tournament positions p and nb-1-p in LDS (two BW-column blocks of stacked
-// columns: m slice rows, then n rows of V).  A round of the block tournament
+// tournament positions p (in registers) and nb-1-p (in LDS): two BW-column
+// blocks of stacked columns, m slice rows, then n rows of V.  A round of the
+// block tournament
 // orthogonalises the two resident blocks against each other; between rounds
 // every block except the one at position 0 moves to the next position
 // (circle method), so a workgroup writes its moving blocks back to their

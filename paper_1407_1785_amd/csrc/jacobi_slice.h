@@ -7,16 +7,16 @@
 // ever waits for another.  The workgroup runs all sweeps of its slice: in
 // every round of the block tournament it visits the round's nb/2 block
 // pairs one after the other, each time loading the two blocks (stacked
-// columns: m slice rows, then n rows of V) from global memory into LDS,
+// columns: m slice rows, then n rows of V; one into registers, one into LDS),
 // orthogonalising them against each other (and, in the first round of a
 // sweep, internally) and writing them back.  With nb = 2 the two blocks stay
-// in LDS for the whole SVD.  The slice stops after a sweep none of whose
+// in registers and LDS for the whole SVD.  The slice stops after a sweep none of whose
 // rotations forces another (rot_forces_sweep), or after max_sweeps.
 //
 // Work split as in jacobi_persist.hip: a column pair per group of PG = 32
 // lanes, BW pairs per step (BW = 4, 8 or 16 columns per block: the block
-// width is chosen per problem so that two blocks of its stacked height fit
-// in LDS), rotation parameters in FP64, norms exact at the start of a round
+// width is chosen per problem so that a block of its stacked height fits in
+// LDS), rotation parameters in FP64, norms exact at the start of a round
 // and tracked through it.
 //
 // Pairs-parallel schedule (jacobi_pairs_kernel) for slices with many
