@@ -191,6 +191,39 @@ JacPlan jacobi_plan(tsvd_handle h, const Geometry& g) {
     return p;
 }
 
+// Tall FP32 slices of few columns take their SVD from the FP64 Gram matrix
+// (tall.hip): up to kMaxGramCols columns (the Cholesky factor's LDS), at least
+// 12 n rows (the n x n matrices and the chunk sums live in the second slice
+// buffer, which the thresholded slice takes last), and where the n x n problem
+// fits the persistent Jacobi.  TSVD_GRAM=0 keeps the global-memory Jacobi,
+// which wider and FP64 slices take.
+template <typename T>
+bool gram_path(tsvd_handle h, const Geometry& g) {
+    return sizeof(T) == 4 && g.n >= 2 && g.n <= kMaxGramCols && g.m >= 12 * g.n && jacobi_tall(g.m, g.n, sizeof(T)) &&
+           env_int("TSVD_GRAM", 1) != 0 && env_int("TSVD_PERSIST", 1) != 0 &&
+           jacobi_persistent_fits(g.n, g.n, g.h, sizeof(double), h->cus, h->lds_cap);
+}
+
+// Its matrices in the second slice buffer: R V, R (then V diag(d) V^H), V of
+// the last prox in FP64, V, and the chunk sums of the Gram matrix.
+struct GramBuffers {
+    cplx<double>*rv, *r, *vprev, *v, *part;
+};
+
+template <typename T>
+GramBuffers gram_buffers(const Geometry& g, const SvtBuffers<T>& sb) {
+    const int64_t vv = (int64_t)g.h * g.n * g.n;
+    cplx<double>* const b = reinterpret_cast<cplx<double>*>(sb.Z);
+    return {b, b + vv, b + 2 * vv, b + 3 * vv, b + 4 * vv};
+}
+
+// The n x n problem's rotation tolerance: a pair left at a relative coupling of
+// 1e-8 moves the result by 1e-8 of the smaller column, and a sweep is the last
+// when its rotations stay under 1e-4 or move the result by less than a
+// sixteenth of the FP32 unit of ||A||_F.
+constexpr double kGramTol = 1e-8;
+constexpr double kGramFloor = 1.1920928955078125e-07 / 16;
+
 // The argument tables of the Jacobi sweeps that run as one launch, uploaded
 // once per call (with the kernels' LDS limit):
 //  entries 0-3, the fallback after a persistent or block-pair launch that
@@ -203,6 +236,33 @@ JacPlan jacobi_plan(tsvd_handle h, const Geometry& g) {
 // counters and block flags from pbar + 4h + 1.
 template <typename T>
 void upload_fallback(tsvd_handle h, const Geometry& g, const SvtBuffers<T>& sb, int max_sweeps) {
+    if (gram_path<T>(h, g)) {
+        // one entry: the n x n FP64 problem
+        const GramBuffers gb = gram_buffers(g, sb);
+        JacSliceArgs<double> a{};
+        a.A = gb.rv;
+        a.V = gb.v;
+        a.m = a.n = g.n;
+        a.h = g.h;
+        a.nb = jacobi_persistent_blocks(g.n);
+        a.tol = kGramTol;
+        a.sweeps = sb.sweeps;
+        a.ctrl = h->ctrl;
+        a.rotations = h->rot_counter + 1;
+        a.max_sweeps = max_sweeps;
+        a.floor_scale = kGramFloor * kGramFloor;
+        a.only_if = sb.pbar + 4 * g.h;
+        const int ws[2] = {0, g.h};
+        char* stage = static_cast<char*>(ensure_host_stage(h, sizeof(a) + sizeof(ws)));
+        std::memcpy(stage, &a, sizeof(a));
+        std::memcpy(stage + sizeof(a), ws, sizeof(ws));
+        hip_check(hipMemcpyAsync(sb.ftab, stage, sizeof(a), hipMemcpyHostToDevice, h->stream), "hipMemcpyAsync");
+        hip_check(hipMemcpyAsync(sb.fws, stage + sizeof(a), sizeof(ws), hipMemcpyHostToDevice, h->stream),
+                  "hipMemcpyAsync");
+        hip_check(prepare_jacobi_slice<double>(16, jacobi_slice_rpt(g.n, g.n)), "jacobi fallback attribute");
+        hip_check(hipStreamSynchronize(h->stream), "hipStreamSynchronize");
+        return;
+    }
     const JacPlan plan = jacobi_plan<T>(h, g);
     if (plan.mode == JacMode::ROUNDS) return;
     const bool pairs = plan.mode == JacMode::PAIRS;
@@ -373,6 +433,142 @@ struct SweepStats {
     const void* v = nullptr;     // V
 };
 
+// Profiling: the sweeps of a one-launch SVD, read back into pending record ip
+// (n(n-1)/2 visited pairs per slice per sweep run); returns the largest.
+template <typename T>
+int record_sweeps(tsvd_handle h, const Geometry& g, const SvtBuffers<T>& sb, int ip, double pair_flops) {
+    const double slice_pairs = 0.5 * g.n * (g.n - 1.0);
+    hip_check(hipMemcpyAsync(h->host_ints, sb.sweeps, sizeof(int) * g.h, hipMemcpyDeviceToHost, h->stream),
+              "hipMemcpyAsync sweeps");
+    hip_check(hipStreamSynchronize(h->stream), "hipStreamSynchronize");
+    int64_t sw = 0;
+    int smax = 0;
+    for (int s = 0; s < g.h; ++s) {
+        sw += h->host_ints[s];
+        smax = std::max(smax, h->host_ints[s]);
+    }
+    if (ip >= 0) {
+        h->pending[ip].work = pair_flops * slice_pairs * (double)sw;
+        h->pending[ip].sweeps = (double)sw;
+        h->pending[ip].pairs = slice_pairs * (double)sw;
+    }
+    return smax;
+}
+
+// C = alpha op(A) diag(dk) op(B) + beta D over square n x n slices (FP64).
+void square_gemm(tsvd_handle h, int kind, const Geometry& g, const cplx<double>* A, int opA, const cplx<double>* B,
+                 int opB, cplx<double>* C, const double* dk = nullptr, const cplx<double>* D = nullptr,
+                 double alpha = 1.0, double beta = 0.0) {
+    ZGemmArgs<double> a{};
+    a.A = A; a.B = B; a.C = C; a.D = D;
+    a.M = a.N = a.K = a.lda = a.ldb = a.ldc = a.ldd = g.n;
+    a.sA = a.sB = a.sC = a.sD = (int64_t)g.n * g.n;
+    a.alpha = alpha; a.beta = beta; a.opA = opA; a.opB = opB; a.batch = g.h;
+    a.dk = dk; a.sdk = g.n; a.kcompact = dk != nullptr;
+    a.ctrl = h->ctrl;
+    prof_launch(h, kind, 8.0 * g.n * g.n * g.n * g.h, [&] { launch_zgemm(a, h->stream); });
+    launch_check("gemm");
+}
+
+// run_svt for tall FP32 slices through the FP64 Gram matrix (tall.hip).  V of
+// the last prox is kept as the slices' FP32 V (what a saved state holds) and
+// made unitary in FP64 again by one Newton-Schulz step, which takes its
+// rounding of 1e-7 to 1e-14.
+SweepStats run_gram(tsvd_handle h, const Geometry& g, const SvtBuffers<float>& sb, int max_sweeps, WarmState* warm,
+                    bool want_rank, bool rebuild) {
+    hipStream_t st = h->stream;
+    const int64_t vv = (int64_t)g.h * g.n * g.n, mn = (int64_t)g.m * g.n;
+    const int vc = warm ? warm->vcur : 0;
+    const GramBuffers b = gram_buffers(g, sb);
+    prof_launch(h, K_GEMM, 8.0 * g.m * g.n * g.n * g.h,
+                [&] { launch_gram(sb.A, g.m, g.n, g.h, g.L == 1, b.part, b.rv, h->ctrl, st); });
+    launch_check("gram");
+    prof_launch(h, K_OTHER, 0.0, [&] { launch_chol(b.rv, g.n, g.h, b.r, h->ctrl, st); });
+    launch_check("cholesky");
+    if (warm && warm->enabled && warm->valid) {
+        launch_convert<float, double>(sb.V[vc], b.vprev, vv, h->ctrl, st);
+        square_gemm(h, K_GEMM, g, b.vprev, 1, b.vprev, 0, b.rv);
+        square_gemm(h, K_GEMM, g, b.vprev, 0, b.rv, 0, b.v, nullptr, b.vprev, -0.5, 1.5);
+    } else {
+        prof_launch(h, K_OTHER, 0.0, [&] { launch_jacobi_seed(b.r, b.v, b.rv, g.n, g.n, g.h, st); });
+        launch_check("jacobi_seed");
+    }
+    square_gemm(h, K_GEMM, g, b.r, 0, b.v, 0, b.rv);
+    JacArgs<double> ja{};
+    ja.A = b.rv;
+    ja.V = b.v;
+    ja.m = ja.n = g.n;
+    ja.h = g.h;
+    ja.nb = jacobi_persistent_blocks(g.n);
+    ja.rot = sb.rot;
+    ja.sweeps = sb.sweeps;
+    ja.rotations = h->rot_counter + 1;
+    ja.tol = kGramTol;
+    ja.ctrl = h->ctrl;
+    ja.clr[0] = sb.pbar;
+    ja.nclr[0] = 4 * g.h;
+    ja.clr[1] = sb.pbar + 4 * g.h + 1;
+    ja.nclr[1] = 1 + g.h * ja.nb;
+    prof_launch(h, K_JAC_INIT, (double)vv * sizeof(cplx<double>), [&] { launch_jacobi_init(ja, st); });
+    launch_check("jacobi_init");
+    ja.clr[0] = ja.clr[1] = nullptr;
+    PersistArgs pa{};
+    pa.pbar = sb.pbar;
+    pa.fro = sb.fro;
+    pa.floor_scale = kGramFloor * kGramFloor;
+    pa.max_sweeps = max_sweeps;
+    pa.spin_limit = std::max(0, env_int("TSVD_PERSIST_SPIN", 1 << 21));
+    const int ip = prof_launch(h, K_JAC_PERSIST, 0.0, [&] {
+        hip_check(launch_jacobi_persistent(ja, pa, h->cus, st), "jacobi_persistent");
+    });
+    hip_check(launch_jacobi_slice<double>(16, jacobi_slice_rpt(g.n, g.n),
+                                          reinterpret_cast<const JacSliceArgs<double>*>(sb.ftab), sb.fws, 1, g.h,
+                                          max_sweeps, st),
+              "jacobi fallback");
+    SweepStats stats;
+    stats.sweeps = -1;   // known on the device only
+    stats.on_device = true;
+    ensure_host_ints(h, g.h);
+    if (h->prof_on) stats.sweeps = record_sweeps(h, g, sb, ip, 48.0 * g.n);
+    prof_launch(h, K_SVT_W, (double)vv * sizeof(cplx<double>) + (double)g.h * g.n * sizeof(double),
+                [&] { launch_svt_sigma(b.rv, g.n, g.n, g.h, sb.sigma, sb.dk, h->ctrl, st); });
+    launch_check("svt_sigma");
+    launch_convert<double, float>(b.v, sb.V[vc], vv, h->ctrl, st);
+    // out = A (V diag(d) V^H), or W = A V
+    if (rebuild) {
+        square_gemm(h, K_GEMM, g, b.v, 0, b.v, 1, b.r, sb.dk);
+        launch_convert<double, float>(b.r, sb.G, vv, h->ctrl, st);
+    }
+    ZGemmArgs<float> gr{};
+    gr.A = sb.A; gr.B = rebuild ? sb.G : sb.V[vc]; gr.C = sb.Z;
+    gr.M = gr.lda = gr.ldc = gr.ldd = g.m;
+    gr.N = gr.K = gr.ldb = g.n;
+    gr.sA = gr.sC = gr.sD = mn; gr.sB = (int64_t)g.n * g.n;
+    gr.alpha = 1.f; gr.batch = g.h; gr.ctrl = h->ctrl;
+    const int ir = prof_launch(h, rebuild ? K_SVT_REBUILD : K_GEMM, 8.0 * g.m * g.n * g.n * g.h,
+                               [&] { launch_zgemm(gr, st); });
+    launch_check("svt_rebuild");
+    if (want_rank || (rebuild && ir >= 0)) {
+        launch_multirank(sb.sigma, g.n, g.n, g.h, h->ctrl, sb.rank, st);
+        launch_check("multirank");
+    }
+    if (rebuild && ir >= 0) {
+        hip_check(hipMemcpyAsync(h->host_ints, sb.rank, sizeof(int) * g.h, hipMemcpyDeviceToHost, st),
+                  "hipMemcpyAsync rank");
+        hip_check(hipStreamSynchronize(st), "hipStreamSynchronize");
+        for (int s = 0; s < g.h; ++s) h->pending[ir].kept += h->host_ints[s];
+    }
+    if (h->prof_on) prof_harvest(h);
+    if (warm) {
+        warm->valid = true;
+        warm->iter += 1;
+    }
+    stats.out = sb.Z;
+    stats.w = rebuild ? nullptr : sb.Z;
+    stats.v = sb.V[vc];
+    return stats;
+}
+
 // Jacobi sweeps + shrink + rebuild on the slices in sb.A; output in sb.Z.
 //
 // Work model of the Jacobi kernels (FP operations): every visited column
@@ -384,6 +580,9 @@ struct SweepStats {
 template <typename T>
 SweepStats run_svt(tsvd_handle h, const Geometry& g, const SvtBuffers<T>& sb, int max_sweeps,
                    WarmState* warm = nullptr, bool want_rank = false, bool rebuild = true) {
+    if constexpr (sizeof(T) == 4) {
+        if (gram_path<T>(h, g)) return run_gram(h, g, sb, max_sweeps, warm, want_rank, rebuild);
+    }
     hipStream_t st = h->stream;
     const bool use_warm = warm && warm->enabled && warm->valid;
     const int64_t nn = (int64_t)g.n * g.n, mn = (int64_t)g.m * g.n;
@@ -458,7 +657,6 @@ SweepStats run_svt(tsvd_handle h, const Geometry& g, const SvtBuffers<T>& sb, in
     ensure_host_ints(h, g.h);
     SweepStats stats;
     const double pair_flops = 28.0 * g.m + 20.0 * g.n;
-    const double slice_pairs = 0.5 * g.n * (g.n - 1.0);
     const JacPlan plan = jacobi_plan<T>(h, g);
     const bool persist = plan.mode == JacMode::PERSIST;
     bool done_persist = false;
@@ -497,24 +695,7 @@ SweepStats run_svt(tsvd_handle h, const Geometry& g, const SvtBuffers<T>& sb, in
             done_persist = true;
             stats.sweeps = -1;   // known on the device only
             stats.on_device = true;
-            if (h->prof_on) {
-                // n(n-1)/2 visited pairs per slice per sweep run
-                hip_check(hipMemcpyAsync(h->host_ints, sb.sweeps, sizeof(int) * g.h, hipMemcpyDeviceToHost, st),
-                          "hipMemcpyAsync sweeps");
-                hip_check(hipStreamSynchronize(st), "hipStreamSynchronize");
-                int64_t sw = 0;
-                int smax = 0;
-                for (int s = 0; s < g.h; ++s) {
-                    sw += h->host_ints[s];
-                    smax = std::max(smax, h->host_ints[s]);
-                }
-                if (ip >= 0) {
-                    h->pending[ip].work = pair_flops * slice_pairs * (double)sw;
-                    h->pending[ip].sweeps = (double)sw;
-                    h->pending[ip].pairs = slice_pairs * (double)sw;
-                }
-                stats.sweeps = smax;
-            }
+            if (h->prof_on) stats.sweeps = record_sweeps(h, g, sb, ip, pair_flops);
         } else {
             (void)hipGetLastError();
             if (ip >= 0) {
@@ -552,23 +733,7 @@ SweepStats run_svt(tsvd_handle h, const Geometry& g, const SvtBuffers<T>& sb, in
         done_persist = true;
         stats.sweeps = -1;   // known on the device only
         stats.on_device = true;
-        if (h->prof_on) {
-            hip_check(hipMemcpyAsync(h->host_ints, sb.sweeps, sizeof(int) * g.h, hipMemcpyDeviceToHost, st),
-                      "hipMemcpyAsync sweeps");
-            hip_check(hipStreamSynchronize(st), "hipStreamSynchronize");
-            int64_t sw = 0;
-            int smax = 0;
-            for (int s = 0; s < g.h; ++s) {
-                sw += h->host_ints[s];
-                smax = std::max(smax, h->host_ints[s]);
-            }
-            if (ip >= 0) {
-                h->pending[ip].work = pair_flops * slice_pairs * (double)sw;
-                h->pending[ip].sweeps = (double)sw;
-                h->pending[ip].pairs = slice_pairs * (double)sw;
-            }
-            stats.sweeps = smax;
-        }
+        if (h->prof_on) stats.sweeps = record_sweeps(h, g, sb, ip, pair_flops);
     }
     if (!done_persist && sb.tall) {
         // tall slices: columns in global memory, two launches per round

@@ -104,11 +104,186 @@ struct Mma<float> {
 // LDS row stride for rows of n elements: n rounded up to 16, plus 4.
 __host__ __device__ constexpr int lds_stride(int n) { return (n + 15) / 16 * 16 + 4; }
 
+// The ADMM arithmetic on one element, shared by the tube and matrix forms.
+template <typename T, int PRO>
+__device__ __forceinline__ T prox_input(T x, T z, T dual, uint8_t seen, double ds) {
+    if (PRO == PRO_COPY) return x;
+    if (PRO == PRO_COMPLETE) {
+        const T q = (T)(ds * (double)dual);
+        const T xo = seen ? x : (T)(z - q);
+        return xo + q;
+    }
+    const T w = (T)(ds * (double)dual);
+    return (x - z) - w;
+}
+
+// Tubes of length 1 (a matrix, as the vectorised baselines solve): the
+// transform is the identity, so a pass is a copy between the tensor's row
+// order and the slice's column order with the ADMM arithmetic on the way.
+// One workgroup per 64 x 64 tile, transposed through LDS when the orders
+// differ; as products with 16 x 16 DFT matrices, one slice column at a time,
+// the passes of a 20480 x 64 matrix read every element at a stride of a row
+// (61 and 66 us, and 41 000 partial sums for the control step).
+constexpr int kMatTile = 64;
+
+__host__ __device__ constexpr int mat_lds_elems() { return kMatTile * (kMatTile + 1); }
+
+// Element e of a thread's 16 in a tile: (row, col) with the tensor's
+// contiguous mode (SLICE: the slice's rows) along the lanes.
+template <typename T>
+struct MatTile {
+    int r0, c0;
+    const Geometry& g;
+    __device__ MatTile(const Geometry& geo, int bid) : g(geo) {
+        const int rt = (geo.m + kMatTile - 1) / kMatTile;
+        c0 = bid / rt * kMatTile;
+        r0 = (bid % rt) * kMatTile;
+    }
+    __device__ bool tensor_rc(int u, int& r, int& c) const {
+        const int a = threadIdx.x & 63, b = (threadIdx.x >> 6) + 4 * u;
+        r = g.trans ? a : b;
+        c = g.trans ? b : a;
+        return r0 + r < g.m && c0 + c < g.n;
+    }
+    __device__ int64_t offset(int r, int c) const {
+        return tube_offset<T>(g, min(r0 + r, g.m - 1), min(c0 + c, g.n - 1));
+    }
+    __device__ bool slice_rc(int u, int& r, int& c) const {
+        r = threadIdx.x & 63;
+        c = (threadIdx.x >> 6) + 4 * u;
+        return r0 + r < g.m && c0 + c < g.n;
+    }
+};
+
+template <typename T, int PRO>
+__device__ __forceinline__ void matrix_forward_body(const FwdArgs<T>& a, int bid, unsigned char* smem) {
+    const Geometry& g = a.g;
+    const MatTile<T> tl(g, bid);
+    T* buf = reinterpret_cast<T*>(smem);   // [col][row]
+    const double ds = (PRO == PRO_COPY) ? 1.0 : a.ctrl->dscale;
+    bool bad = false;
+    constexpr int U = 8;
+#pragma unroll
+    for (int u0 = 0; u0 < 16; u0 += U) {
+        T xv[U], zv[U], qv[U];
+        uint8_t mv[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            int r, c;
+            (void)tl.tensor_rc(u0 + u, r, c);
+            const int64_t e = tl.offset(r, c);
+            xv[u] = a.x[e];
+            zv[u] = PRO == PRO_COMPLETE ? a.z[e] : (PRO == PRO_RPCA ? a.s[e] : (T)0);
+            qv[u] = PRO == PRO_COPY ? (T)0 : a.dual[e];
+            mv[u] = PRO == PRO_COMPLETE ? a.mask[e] : (uint8_t)0;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            int r, c;
+            const bool in = tl.tensor_rc(u0 + u, r, c);
+            const T v = prox_input<T, PRO>(xv[u], zv[u], qv[u], mv[u], ds);
+            if (in) bad |= !isfinite(v);
+            buf[c * (kMatTile + 1) + r] = v;
+        }
+    }
+    if (bad) *a.nonfinite = 1;
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+        int r, c;
+        if (tl.slice_rc(u, r, c))
+            a.out[(int64_t)(tl.c0 + c) * g.m + tl.r0 + r] = cplx<T>{buf[c * (kMatTile + 1) + r], (T)0};
+    }
+}
+
+template <typename T, int EPI>
+__device__ __forceinline__ void matrix_inverse_body(const InvArgs<T>& a, int bid, unsigned char* smem) {
+    const Geometry& g = a.g;
+    const MatTile<T> tl(g, bid);
+    T* buf = reinterpret_cast<T*>(smem);
+    double* red = reinterpret_cast<double*>(smem + (mat_lds_elems() * sizeof(T) + 15) / 16 * 16);
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+        int r, c;
+        if (tl.slice_rc(u, r, c))
+            buf[c * (kMatTile + 1) + r] = a.in[(int64_t)(tl.c0 + c) * g.m + tl.r0 + r].re;
+    }
+    __syncthreads();
+    double part[kNumPartials] = {0.0, 0.0, 0.0, 0.0};
+    double ds = 1.0, thr = 0.0;
+    if (EPI != EPI_STORE) {
+        ds = a.ctrl->dscale;
+        thr = a.ctrl->shrink;
+    }
+    constexpr int U = 4;
+#pragma unroll
+    for (int u0 = 0; u0 < 16; u0 += U) {
+        T v0[U], v1[U], v2[U], v3[U];
+        uint8_t mk[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            int r, c;
+            (void)tl.tensor_rc(u0 + u, r, c);
+            const int64_t e = tl.offset(r, c);
+            if (EPI == EPI_COMPLETE) {
+                v0[u] = a.z_old[e];
+                v1[u] = a.dual_old[e];
+                v2[u] = a.y[e];
+                mk[u] = a.mask[e];
+            } else if (EPI != EPI_STORE) {
+                v0[u] = a.m[e];
+                v1[u] = a.dual_old[e];
+                v2[u] = a.l_old[e];
+                v3[u] = a.s_old[e];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            int r, c;
+            if (!tl.tensor_rc(u0 + u, r, c)) continue;
+            const int64_t e = tl.offset(r, c);
+            const T zv = buf[c * (kMatTile + 1) + r];
+            if (EPI == EPI_STORE) {
+                a.out[e] = zv;
+            } else if (EPI == EPI_COMPLETE) {
+                const T q = (T)(ds * (double)v1[u]);
+                const T x = mk[u] ? v2[u] : (T)(v0[u] - q);
+                a.out[e] = zv;
+                a.dual_new[e] = (q + x) - zv;
+                part[0] += (double)sq(x - zv);
+                part[1] += (double)sq(zv - v0[u]);
+            } else {
+                const T w = (T)(ds * (double)v1[u]);
+                const T d = (v0[u] - w) - zv;
+                T sn;
+                if (EPI == EPI_RPCA_L1) {
+                    const T mag = (T)fmax(fabs(d) - (T)thr, (T)0);
+                    sn = d > (T)0 ? mag : (d < (T)0 ? -mag : (T)0);
+                } else {   // a tube of one element
+                    const T nrm = (T)sqrt((double)d * (double)d);
+                    sn = d * (nrm > (T)0 ? (T)fmax((T)1 - (T)thr / nrm, (T)0) : (T)0);
+                }
+                a.out[e] = zv;
+                a.s_new[e] = sn;
+                a.dual_new[e] = ((w + zv) + sn) - v0[u];
+                part[0] += (double)sq((zv + sn) - v0[u]);
+                part[1] += (double)sq(zv - v2[u]);
+                part[2] += (double)sq(sn - v3[u]);
+            }
+        }
+    }
+    if (EPI != EPI_STORE) {
+        __syncthreads();
+        block_partials(part, a.partials, red, bid);
+    }
+}
+
 }  // namespace
 
 template <typename T, int PRO>
 __device__ __forceinline__ void dft_forward_body(const FwdArgs<T>& a, int bid, unsigned char* smem) {
     const Geometry& g = a.g;
+    if (g.L == 1) return matrix_forward_body<T, PRO>(a, bid, smem);
     const DftDims d = DftDims::of(g.h, g.L);
     const int L = g.L, tile = a.tile, ldb = lds_stride(d.Lk);
     T* buf = reinterpret_cast<T*>(smem);   // tile x ldb, tube r at row r
@@ -145,17 +320,7 @@ __device__ __forceinline__ void dft_forward_body(const FwdArgs<T>& a, int bid, u
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int idx = base + u * (int)blockDim.x;
-            T v;
-            if (PRO == PRO_COPY) {
-                v = xv[u];
-            } else if (PRO == PRO_COMPLETE) {
-                const T q = (T)(ds * (double)qv[u]);
-                const T x = mv[u] ? xv[u] : (T)(zv[u] - q);
-                v = x + q;
-            } else {
-                const T w = (T)(ds * (double)qv[u]);
-                v = (xv[u] - zv[u]) - w;
-            }
+            const T v = prox_input<T, PRO>(xv[u], zv[u], qv[u], mv[u], ds);
             if (idx < total) {
                 const int r = idx / L, t = idx - r * L;
                 bad |= !isfinite(v);
@@ -228,6 +393,7 @@ __device__ __forceinline__ void dft_forward_body(const FwdArgs<T>& a, int bid, u
 template <typename T, int EPI>
 __device__ __forceinline__ void dft_inverse_body(const InvArgs<T>& a, int bid, unsigned char* smem) {
     const Geometry& g = a.g;
+    if (g.L == 1) return matrix_inverse_body<T, EPI>(a, bid, smem);
     const int L = g.L, tile = a.tile, h = g.h;
     const DftDims d = DftDims::of(h, L);
     const int ldl = lds_stride(d.Lr);
@@ -502,11 +668,13 @@ int dft_inverse_tile(const Geometry& g, int epilogue) {
 }
 
 int64_t dft_grid(const Geometry& g, int tile) {
+    if (g.L == 1) return (int64_t)((g.n + kMatTile - 1) / kMatTile) * ((g.m + kMatTile - 1) / kMatTile);
     return (int64_t)g.n * ((g.m + tile - 1) / tile);
 }
 
 template <typename T>
 size_t dft_forward_lds(const Geometry& g, int tile) {
+    if (g.L == 1) return mat_lds_elems() * sizeof(T);
     const DftDims d = DftDims::of(g.h, g.L);
     return (size_t)tile * lds_stride(d.Lk) * sizeof(T);
 }
@@ -514,6 +682,7 @@ size_t dft_forward_lds(const Geometry& g, int tile) {
 template <typename T>
 size_t dft_inverse_lds(const Geometry& g, int tile, int epilogue) {
     (void)epilogue;
+    if (g.L == 1) return mat_lds_elems() * sizeof(T) + 16 + 64 * sizeof(double);
     const DftDims d = DftDims::of(g.h, g.L);
     const size_t lds = (size_t)g.h * tile * sizeof(cplx<T>) + (size_t)tile * lds_stride(d.Lr) * sizeof(T);
     return lds + 64 * sizeof(double) + (size_t)tile * sizeof(T) + 16;

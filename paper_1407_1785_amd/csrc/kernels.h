@@ -298,6 +298,14 @@ void launch_jacobi_tall_round(const JacArgs<T>& a, const TallPlan& t, double* pa
 bool jacobi_seed_fits(int m, int n);
 void launch_jacobi_seed(const cplx<double>* A, cplx<double>* V, cplx<double>* G, int m, int n, int h,
                         hipStream_t st);
+// Tall FP32 slices through their FP64 Gram matrix (tall.hip).
+constexpr int kMaxGramCols = 96;
+int gram_chunks(int m, int n);   // row chunks: partial holds gram_chunks x h x n x n values
+void launch_gram(const cplx<float>* A, int m, int n, int h, bool real, cplx<double>* partial, cplx<double>* G,
+                 const Ctrl* ctrl, hipStream_t st);
+void launch_chol(const cplx<double>* G, int n, int h, cplx<double>* R, const Ctrl* ctrl, hipStream_t st);
+template <typename S, typename D>
+void launch_convert(const cplx<S>* src, cplx<D>* dst, int64_t n, const Ctrl* ctrl, hipStream_t st);
 // LDS bytes one workgroup may use on the current device
 void jacobi_set_lds_limit(size_t bytes);
 
