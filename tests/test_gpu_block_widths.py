@@ -1,0 +1,41 @@
+"""Jacobi block pairs narrower than the pair groups of a workgroup: the ring of
+cross steps closes over the columns there are.  Widths of 1 to 16, equal and
+one apart, odd and even, in the single-problem and both batched schedules,
+against the FP64 oracle."""
+
+import numpy as np
+import pytest
+
+import paper_1407_1785_amd as lib
+from oracle import admm
+from tests.gpu_util import announce, rel_fro, to_gpu, torch_cuda
+
+pytestmark = pytest.mark.gpu
+
+# block widths: 1; 1, 2; 2, 3; 8, 9; 9; 15, 16; 16; 8, 9 in four blocks; 12; 14, 15; 16
+WIDTHS = [2, 3, 5, 17, 18, 31, 32, 33, 72, 87, 96]
+
+
+@pytest.mark.parametrize("n", WIDTHS)
+@pytest.mark.parametrize("batch", [False, True])
+def test_narrow_blocks(monkeypatch, n, batch):
+    torch = torch_cuda()
+    rng = np.random.default_rng(n)
+    x = rng.normal(size=(n + 5, n, 2))
+    mask = (rng.random(x.shape) < 0.6).astype(np.uint8)
+    ref = admm.complete(x * mask, mask, max_iter=3, tol=0.0)["X"]
+    announce("block widths", n, batch)
+    if not batch:
+        out, _ = lib.tsvd_complete(to_gpu(torch, x * mask), to_gpu(torch, mask), 1e-2, 0.0, max_iter=3)
+        assert rel_fro(out.cpu().numpy(), ref) <= 1e-10
+        return
+    monkeypatch.setenv("TSVD_TUNE", "0")
+    monkeypatch.setenv("TSVD_BATCH_BW", "16")
+    for pairs_min in ("1", "99"):
+        monkeypatch.setenv("TSVD_PAIRS_MIN", pairs_min)
+        h = lib.Handle(0, 1 << 28)
+        p = lib.complete_problem(to_gpu(torch, x * mask), to_gpu(torch, mask), 1e-2, 0.0, max_iter=3)
+        (status, _), = lib.batch_run([p], handle=h)
+        h.close()
+        assert status == 0
+        assert rel_fro(p.out.cpu().numpy(), ref) <= 1e-10
