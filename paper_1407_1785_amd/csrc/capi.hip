@@ -224,11 +224,39 @@ GramBuffers gram_buffers(const Geometry& g, const SvtBuffers<T>& sb) {
 constexpr double kGramTol = 1e-8;
 constexpr double kGramFloor = 1.1920928955078125e-07 / 16;
 
+// Words of the Jacobi launch of a geometry, from pbar; zero before the first
+// SVD of a call (clear_persist_words) and again after every SVD.
+template <typename T>
+int persist_words(tsvd_handle h, const Geometry& g) {
+    if (gram_path<T>(h, g)) return 4 * g.h + 2 + g.h * jacobi_persistent_blocks(g.n);
+    const JacPlan plan = jacobi_plan<T>(h, g);
+    if (plan.mode == JacMode::PERSIST) return 4 * g.h + 2 + g.h * jacobi_persistent_blocks(g.n);
+    return 4 * g.h + 1 + (plan.mode == JacMode::PAIRS ? g.h * (1 + plan.nb) : 0);
+}
+
+// Workgroups that share a slice in the launch that ends an SVD: eight columns
+// each, one workgroup per CU at most.
+inline int finish_parts(tsvd_handle h, const Geometry& g) {
+    return std::max(1, std::min((g.n + 7) / 8, h->cus / g.h));
+}
+
+// The launch that ends an SVD (the gated fallback) writes the singular values
+// and clears the Jacobi words.
+template <typename T, typename E>
+void finish_args(tsvd_handle h, const Geometry& g, const SvtBuffers<T>& sb, JacSliceArgs<E>& a) {
+    a.sigma = sb.sigma;
+    a.dk = sb.dk;
+    a.parts = finish_parts(h, g);
+    a.clr = sb.pbar;
+    a.nclr = persist_words<T>(h, g);
+}
+
 // The argument tables of the Jacobi sweeps that run as one launch, uploaded
 // once per call (with the kernels' LDS limit):
-//  entries 0-3, the fallback after a persistent or block-pair launch that
-//  gave up: the one-workgroup-per-slice kernel on the same slices (work
-//  buffer A or Z, V buffer 0 or 1), gated on the error word at pbar + 4h;
+//  entries 0-3, the end of the SVD: the one-workgroup-per-slice kernel on the
+//  same slices (work buffer A or Z, V buffer 0 or 1), whose sweeps are the
+//  fallback after a persistent or block-pair launch that gave up, gated on the
+//  error word at pbar + 4h, and which writes the singular values;
 //  entries 4-7 (PAIRS only), the block-pair kernel on the same buffers.
 // In PAIRS mode the persistent kernel's int words hold the block-pair
 // kernel's: the rotation-flag ring at pbar, the role ticket at pbar + 4h - 1
@@ -252,7 +280,8 @@ void upload_fallback(tsvd_handle h, const Geometry& g, const SvtBuffers<T>& sb, 
         a.max_sweeps = max_sweeps;
         a.floor_scale = kGramFloor * kGramFloor;
         a.only_if = sb.pbar + 4 * g.h;
-        const int ws[2] = {0, g.h};
+        finish_args(h, g, sb, a);
+        const int ws[2] = {0, g.h * a.parts};
         char* stage = static_cast<char*>(ensure_host_stage(h, sizeof(a) + sizeof(ws)));
         std::memcpy(stage, &a, sizeof(a));
         std::memcpy(stage + sizeof(a), ws, sizeof(ws));
@@ -284,13 +313,14 @@ void upload_fallback(tsvd_handle h, const Geometry& g, const SvtBuffers<T>& sb, 
         a.floor_scale = jacobi_floor_scale(g.m, sizeof(T));
         if (k < 4) {
             a.only_if = sb.pbar + 4 * g.h;
+            finish_args(h, g, sb, a);
         } else {
             a.rot = sb.pbar;
             a.bar = sb.pbar + 4 * g.h + 1;
             a.fro = sb.fro;
         }
     }
-    const int ws[4] = {0, g.h, 0, pairs ? g.h * (plan.nb / 2) : 0};
+    const int ws[4] = {0, g.h * tab[0].parts, 0, pairs ? g.h * (plan.nb / 2) : 0};
     char* stage = static_cast<char*>(ensure_host_stage(h, sizeof(tab) + sizeof(ws)));
     std::memcpy(stage, tab, sizeof(tab));
     std::memcpy(stage + sizeof(tab), ws, sizeof(ws));
@@ -505,13 +535,6 @@ SweepStats run_gram(tsvd_handle h, const Geometry& g, const SvtBuffers<float>& s
     ja.rotations = h->rot_counter + 1;
     ja.tol = kGramTol;
     ja.ctrl = h->ctrl;
-    ja.clr[0] = sb.pbar;
-    ja.nclr[0] = 4 * g.h;
-    ja.clr[1] = sb.pbar + 4 * g.h + 1;
-    ja.nclr[1] = 1 + g.h * ja.nb;
-    prof_launch(h, K_JAC_INIT, (double)vv * sizeof(cplx<double>), [&] { launch_jacobi_init(ja, st); });
-    launch_check("jacobi_init");
-    ja.clr[0] = ja.clr[1] = nullptr;
     PersistArgs pa{};
     pa.pbar = sb.pbar;
     pa.fro = sb.fro;
@@ -521,18 +544,17 @@ SweepStats run_gram(tsvd_handle h, const Geometry& g, const SvtBuffers<float>& s
     const int ip = prof_launch(h, K_JAC_PERSIST, 0.0, [&] {
         hip_check(launch_jacobi_persistent(ja, pa, h->cus, st), "jacobi_persistent");
     });
-    hip_check(launch_jacobi_slice<double>(16, jacobi_slice_rpt(g.n, g.n),
-                                          reinterpret_cast<const JacSliceArgs<double>*>(sb.ftab), sb.fws, 1, g.h,
-                                          max_sweeps, st),
-              "jacobi fallback");
     SweepStats stats;
     stats.sweeps = -1;   // known on the device only
     stats.on_device = true;
     ensure_host_ints(h, g.h);
+    prof_launch(h, K_SVT_W, (double)vv * sizeof(cplx<double>) + (double)g.h * g.n * sizeof(double), [&] {
+        hip_check(launch_jacobi_slice<double>(16, jacobi_slice_rpt(g.n, g.n),
+                                              reinterpret_cast<const JacSliceArgs<double>*>(sb.ftab), sb.fws, 1,
+                                              g.h * finish_parts(h, g), max_sweeps, st),
+                  "jacobi fallback");
+    });
     if (h->prof_on) stats.sweeps = record_sweeps(h, g, sb, ip, 48.0 * g.n);
-    prof_launch(h, K_SVT_W, (double)vv * sizeof(cplx<double>) + (double)g.h * g.n * sizeof(double),
-                [&] { launch_svt_sigma(b.rv, g.n, g.n, g.h, sb.sigma, sb.dk, h->ctrl, st); });
-    launch_check("svt_sigma");
     launch_convert<double, float>(b.v, sb.V[vc], vv, h->ctrl, st);
     // out = A (V diag(d) V^H), or W = A V
     if (rebuild) {
@@ -659,21 +681,21 @@ SweepStats run_svt(tsvd_handle h, const Geometry& g, const SvtBuffers<T>& sb, in
     const double pair_flops = 28.0 * g.m + 20.0 * g.n;
     const JacPlan plan = jacobi_plan<T>(h, g);
     const bool persist = plan.mode == JacMode::PERSIST;
+    const int entry = (work == sb.Z ? 2 : 0) + vc;   // of the argument tables
+    int jac_ip = -1;   // timing record of the one-launch sweeps
     bool done_persist = false;
+    // a cold start without a seed: V = I (a warm or seeded one has its V, and
+    // the Jacobi words are clear: one launch of 4.5 us less per iteration)
+    auto reset_v = [&] {
+        if (!ja.reset_v) return;
+        prof_launch(h, K_JAC_INIT, (double)g.h * g.n * g.n * sizeof(cplx<T>), [&] { launch_jacobi_init(ja, st); });
+        launch_check("jacobi_init");
+    };
     if (persist) {
         // one launch runs every sweep
         ja.nb = jacobi_persistent_blocks(g.n);
         ja.rotations = h->rot_counter + 1;
-        // the init also clears the barrier counters, rotation flags, role
-        // ticket and block flags (the error word is cleared once per call)
-        ja.clr[0] = sb.pbar;
-        ja.nclr[0] = 4 * g.h;
-        ja.clr[1] = sb.pbar + 4 * g.h + 1;
-        ja.nclr[1] = 1 + g.h * ja.nb;
-        prof_launch(h, K_JAC_INIT, (double)g.h * g.n * g.n * sizeof(cplx<T>),
-                    [&] { launch_jacobi_init(ja, st); });
-        launch_check("jacobi_init");
-        ja.clr[0] = ja.clr[1] = nullptr;
+        reset_v();
         PersistArgs pa{};
         pa.pbar = sb.pbar;
         pa.fro = sb.fro;
@@ -686,16 +708,10 @@ SweepStats run_svt(tsvd_handle h, const Geometry& g, const SvtBuffers<T>& sb, in
         const int ip = prof_launch(h, K_JAC_PERSIST, 0.0,
                                    [&] { e = launch_jacobi_persistent(ja, pa, h->cus, st); });
         if (e == hipSuccess) {
-            // finishes the SVD only if a wait of the persistent launch gave up
-            hip_check(launch_jacobi_slice<T>(plan.bw, plan.rpt, sb.ftab + (work == sb.Z ? 2 : 0) + vc,
-                                             sb.fws, 1, g.h, max_sweeps, st),
-                      "jacobi fallback");
-        }
-        if (e == hipSuccess) {
             done_persist = true;
             stats.sweeps = -1;   // known on the device only
             stats.on_device = true;
-            if (h->prof_on) stats.sweeps = record_sweeps(h, g, sb, ip, pair_flops);
+            jac_ip = ip;
         } else {
             (void)hipGetLastError();
             if (ip >= 0) {
@@ -707,33 +723,18 @@ SweepStats run_svt(tsvd_handle h, const Geometry& g, const SvtBuffers<T>& sb, in
         }
     }
     if (plan.mode == JacMode::PAIRS) {
-        // one launch runs every sweep, one workgroup per block pair; the init
-        // clears the rotation-flag ring, the role ticket, the barrier counters
-        // and the block flags (the error word is cleared once per call)
-        ja.nb = plan.nb;
-        ja.rotations = h->rot_counter + 1;
-        ja.clr[0] = sb.pbar;
-        ja.nclr[0] = 4 * g.h;
-        ja.clr[1] = sb.pbar + 4 * g.h + 1;
-        ja.nclr[1] = g.h * (1 + plan.nb);
-        prof_launch(h, K_JAC_INIT, (double)g.h * g.n * g.n * sizeof(cplx<T>),
-                    [&] { launch_jacobi_init(ja, st); });
-        launch_check("jacobi_init");
-        ja.clr[0] = ja.clr[1] = nullptr;
-        const int entry = (work == sb.Z ? 2 : 0) + vc;
+        // one launch runs every sweep, one workgroup per block pair
+        reset_v();
         const int spin = std::max(0, env_int("TSVD_PERSIST_SPIN", 1 << 21));
         const int ip = prof_launch(h, K_JAC_PERSIST, 0.0, [&] {
             hip_check(launch_jacobi_pairs<T>(plan.bw, plan.rpt, sb.ftab + 4 + entry, sb.fws + 2, 1,
                                              g.h * (plan.nb / 2), sb.pbar + 4 * g.h - 1, spin, st),
                       "jacobi block pairs");
         });
-        // finishes the SVD only if a wait between the workgroups gave up
-        hip_check(launch_jacobi_slice<T>(plan.bw, plan.rpt, sb.ftab + entry, sb.fws, 1, g.h, max_sweeps, st),
-                  "jacobi fallback");
         done_persist = true;
         stats.sweeps = -1;   // known on the device only
         stats.on_device = true;
-        if (h->prof_on) stats.sweeps = record_sweeps(h, g, sb, ip, pair_flops);
+        jac_ip = ip;
     }
     if (!done_persist && sb.tall) {
         // tall slices: columns in global memory, two launches per round
@@ -806,9 +807,17 @@ SweepStats run_svt(tsvd_handle h, const Geometry& g, const SvtBuffers<T>& sb, in
     }
     // sigma_j = ||w_j||, then Zhat = W diag((1 - tau/sigma)_+) V^H on the matrix cores
     const int64_t slice_bytes = (int64_t)g.h * g.m * g.n * sizeof(cplx<T>);
-    prof_launch(h, K_SVT_W, (double)slice_bytes + (double)g.h * g.n * sizeof(double),
-                [&] { launch_svt_sigma(work, g.m, g.n, g.h, sb.sigma, sb.dk, h->ctrl, st); });
+    prof_launch(h, K_SVT_W, (double)slice_bytes + (double)g.h * g.n * sizeof(double), [&] {
+        if (stats.on_device)
+            // with the sweeps that a launch whose waits gave up has left
+            hip_check(launch_jacobi_slice<T>(plan.bw, plan.rpt, sb.ftab + entry, sb.fws, 1,
+                                             g.h * finish_parts(h, g), max_sweeps, st),
+                      "jacobi fallback");
+        else
+            launch_svt_sigma(work, g.m, g.n, g.h, sb.sigma, sb.dk, h->ctrl, st);
+    });
     launch_check("svt_sigma");
+    if (h->prof_on && stats.on_device) stats.sweeps = record_sweeps(h, g, sb, jac_ip, pair_flops);
     ZGemmArgs<T> gr{};
     gr.A = work; gr.B = sb.V[vc]; gr.C = out;
     gr.M = g.m; gr.N = g.n; gr.K = g.n;
@@ -922,13 +931,13 @@ LoopResult admm_loop(tsvd_handle h, int max_iter, F&& iteration) {
 
 void clear_flag(tsvd_handle h) { launch_fill<int>(h->flag, 0, 1, h->stream); }
 
-// Error word of the persistent Jacobi launches (pbar[4h]): cleared once per
-// call; bit 1 (a wait between workgroups gave up) only makes the fallback
-// kernel finish the SVDs, bit 2 (a wait inside a workgroup ran out: a fault)
-// fails the call.
+// Words of the one-launch Jacobi sweeps, cleared once per call (then by the end
+// of every SVD, but for the error word).  Error word, pbar[4h]: bit 1 (a wait
+// between workgroups gave up) only makes the fallback kernel finish the SVDs,
+// bit 2 (a wait inside a workgroup ran out: a fault) fails the call.
 template <typename T>
-void clear_persist_err(tsvd_handle h, const Geometry& g, const SvtBuffers<T>& sb) {
-    launch_fill<int>(sb.pbar + 4 * g.h, 0, 1, h->stream);
+void clear_persist_words(tsvd_handle h, const Geometry& g, const SvtBuffers<T>& sb) {
+    launch_fill<int>(sb.pbar, 0, persist_words<T>(h, g), h->stream);
 }
 
 template <typename T>
@@ -1009,7 +1018,7 @@ void do_tsvt(tsvd_handle h, const void* X, tsvd_shape shape, tsvd_dtype dtype, d
         c.dscale = 1.0;
         put_ctrl(h, c);
         clear_flag(h);
-        clear_persist_err(h, g, sb);
+        clear_persist_words(h, g, sb);
 
         FwdArgs<T> fa{};
         fa.x = static_cast<const T*>(X);
@@ -1074,7 +1083,7 @@ SvdStage<T> svd_stage(tsvd_handle h, const Geometry& g, const void* X, size_t ex
     c.dscale = 1.0;
     put_ctrl(h, c);
     clear_flag(h);
-    clear_persist_err(h, g, st.sb);
+    clear_persist_words(h, g, st.sb);
     FwdArgs<T> fa{};
     fa.x = static_cast<const T*>(X);
     fa.ctrl = h->ctrl;
@@ -1261,7 +1270,7 @@ void do_complete(tsvd_handle h, const void* X_obs, const uint8_t* mask, tsvd_sha
         launch_set_tol(h->ctrl, sb.partials, elementwise_parts(), tol, st);
         launch_check("setup");
         clear_flag(h);
-        clear_persist_err(h, g, sb);
+        clear_persist_words(h, g, sb);
 
         FwdArgs<T> fa{};
         fa.x = Y;
@@ -1414,7 +1423,7 @@ void do_trpca(tsvd_handle h, const void* X, tsvd_shape shape, tsvd_dtype dtype, 
         launch_set_tol(h->ctrl, sb.partials, elementwise_parts(), tol, st);
         launch_check("setup");
         clear_flag(h);
-        clear_persist_err(h, g, sb);
+        clear_persist_words(h, g, sb);
 
         FwdArgs<T> fa{};
         fa.x = M;

@@ -12,7 +12,9 @@
 // (circle method), so a workgroup writes its moving blocks back to their
 // home columns in global memory, meets the other workgroups of its slice at
 // a barrier, and reads the blocks of its next positions.  The first round of
-// every sweep also orthogonalises each block internally.
+// every sweep also orthogonalises each block internally.  A slice of one
+// block pair (n <= 32) shares no word with others and meets nobody: 32 x 32 x
+// 16 FP64 completion 152 -> 148 us an iteration.
 //
 // Work split.  A column pair is handled by a group of PG = 32 lanes (two DPP
 // rows), so a 512-thread workgroup (two waves per SIMD) works on BW = 16
@@ -200,11 +202,14 @@ __global__ __launch_bounds__(PBW * PG) void jacobi_persistent_kernel(JacArgs<T> 
     if (p.floor_scale > 0.0) {
         const double part =
             pair_fro_part<T, PG, RPT, PBW>(x, blk1, width(player0), width(player1), ldc, ka, jnorm);
-        if (threadIdx.x == 0) coh_store_f64(p.fro + (int64_t)s * G + wg, part);
-        arrivals += G;
-        if (!slice_barrier(counter, arrivals, err, p.spin_limit)) {
-            alive = false;   // giving up before any rotation: both blocks are still home
-        } else {
+        if (G > 1) {
+            if (threadIdx.x == 0) coh_store_f64(p.fro + (int64_t)s * G + wg, part);
+            arrivals += G;
+            alive = slice_barrier(counter, arrivals, err, p.spin_limit);
+        }
+        if (G == 1) {
+            floor2 = p.floor_scale * part;
+        } else if (alive) {   // otherwise giving up before any rotation: both blocks are still home
             if (threadIdx.x == 0) {
                 double fro2 = 0.0;
                 for (int i = 0; i < G; ++i) fro2 += coh_load_f64(p.fro + (int64_t)s * G + i);
@@ -234,7 +239,7 @@ __global__ __launch_bounds__(PBW * PG) void jacobi_persistent_kernel(JacArgs<T> 
             if (last) {
                 if (nbig && l == 0) rot_any = 1;
                 __syncthreads();
-                if (threadIdx.x == 0 && rot_any)
+                if (G > 1 && threadIdx.x == 0 && rot_any)
                     __hip_atomic_fetch_or(rotflag + (sweep % 3) * a.h + s, 1, __ATOMIC_RELAXED,
                                           __HIP_MEMORY_SCOPE_AGENT);
             }
@@ -246,15 +251,18 @@ __global__ __launch_bounds__(PBW * PG) void jacobi_persistent_kernel(JacArgs<T> 
             if (last) {
                 // end of the sweep: every workgroup of the slice meets, then all
                 // read the same rotation flag and stop together when it is clear
+                // (a slice of one block pair asks its own flag: no word is shared)
                 arrivals += G;
-                if (!slice_barrier(counter, arrivals, err, p.spin_limit)) {
+                if (G > 1 && !slice_barrier(counter, arrivals, err, p.spin_limit)) {
                     home0 = next0 == player0;   // giving up
                     home1 = next1 == player1;
                     alive = false;
                     break;
                 }
-                if (threadIdx.x == 0) stop = __hip_atomic_load(rotflag + (sweep % 3) * a.h + s,
-                                                              __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0;
+                if (threadIdx.x == 0)
+                    stop = (G == 1 ? rot_any
+                                   : __hip_atomic_load(rotflag + (sweep % 3) * a.h + s, __ATOMIC_RELAXED,
+                                                       __HIP_MEMORY_SCOPE_AGENT)) == 0;
                 __syncthreads();
                 if (stop) {
                     home0 = next0 == player0;   // converged

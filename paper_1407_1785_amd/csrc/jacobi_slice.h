@@ -28,8 +28,8 @@
 // wg_start[p] <= b < wg_start[p + 1], slice b - wg_start[p].  A problem
 // whose ADMM has stopped (ctrl->done) is skipped, and so is one whose
 // optional only_if word is zero (the single-problem driver's fallback after
-// a persistent launch that gave up); each slice raises ctrl->sweep_max to
-// its sweep count.
+// a persistent launch that gave up, which also writes the singular values);
+// each slice raises ctrl->sweep_max to its sweep count.
 
 #pragma once
 
@@ -43,18 +43,13 @@ using namespace jac;
 
 constexpr int kPGs = 32;
 
+// All sweeps of slice s by this workgroup.
 template <typename T, int BW, int RPT>
-__global__ __launch_bounds__(BW * kPGs, (jacobi_waves_per_simd<T, kPGs, BW, RPT>())) void jacobi_slice_kernel(const JacSliceArgs<T>* tab, const int* wg_start,
-                                                                  int nprob, int max_sweeps) {
+__device__ __forceinline__ void slice_svd(const JacSliceArgs<T>& a, int s, int max_sweeps) {
     constexpr int PG = kPGs, NT = BW * PG;
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ int rot_any;
     __shared__ double jnorm[BW];
-    const int p = batch_find(wg_start, nprob, (int)blockIdx.x);
-    const JacSliceArgs<T>& a = tab[p];
-    if (a.ctrl && a.ctrl->done) return;
-    if (a.only_if && *a.only_if == 0) return;
-    const int s = (int)blockIdx.x - wg_start[p];
     const int m = a.m, n = a.n, nb = a.nb, G = nb / 2;
     const int ka = (m + PG - 1) / PG;
     const int ldc = PG * RPT + 1;   // one more than the column: a wave's groups read different LDS banks
@@ -120,6 +115,43 @@ __global__ __launch_bounds__(BW * kPGs, (jacobi_waves_per_simd<T, kPGs, BW, RPT>
         if (a.ctrl) atomicMax(&a.ctrl->sweep_max, sweeps);
     }
     if (l == 0 && nrot && a.rotations) atomicAdd(a.rotations, (unsigned long long)nrot);
+}
+
+template <typename T, int BW, int RPT>
+__global__ __launch_bounds__(BW * kPGs, (jacobi_waves_per_simd<T, kPGs, BW, RPT>()))
+void jacobi_slice_kernel(const JacSliceArgs<T>* tab, const int* wg_start, int nprob, int max_sweeps) {
+    const int p = batch_find(wg_start, nprob, (int)blockIdx.x);
+    const JacSliceArgs<T>& a = tab[p];
+    if (a.ctrl && a.ctrl->done) return;
+    const int idx = (int)blockIdx.x - wg_start[p];
+    const bool run = !a.only_if || *a.only_if != 0;
+    if (!a.sigma) {
+        if (run) slice_svd<T, BW, RPT>(a, idx, max_sweeps);
+        return;
+    }
+    // The last launch of a single problem's SVD: the sweeps are over unless
+    // the launch that ran them gave up, and what is left is to write the
+    // singular values and clear the words for the next SVD.  `parts`
+    // workgroups share a slice's columns; a slice whose sweeps are still to be
+    // run is one workgroup's.
+    // (A gated fallback, svt_sigma and a launch that clears the words are
+    // 4.5 us each; 32 x 32 x 16 FP64 completion 148 -> 144 us an iteration,
+    // larger shapes the same.)
+    const int s = idx / a.parts, part = idx - s * a.parts;
+    if (run) {
+        if (part != 0) return;
+        slice_svd<T, BW, RPT>(a, s, max_sweeps);
+        __syncthreads();
+    }
+    constexpr int NW = BW * kPGs / 64;
+    const int wave = threadIdx.x >> 6;
+    const cplx<T>* const W = a.A + (int64_t)s * a.n * a.m;
+    for (int j = (run ? 0 : part * NW) + wave; j < a.n; j += run ? NW : a.parts * NW)
+        sigma_column(W + (int64_t)j * a.m, a.m, a.ctrl->tau, a.sigma + (int64_t)s * a.n + j,
+                     a.dk + (int64_t)s * a.n + j);
+    if (part == 0)
+        for (int i = s * BW * kPGs + threadIdx.x; i < a.nclr; i += a.h * BW * kPGs)
+            if (a.clr + i != a.only_if) a.clr[i] = 0;
 }
 
 // Pairs-parallel schedule: nb / 2 workgroups per slice, one per block pair

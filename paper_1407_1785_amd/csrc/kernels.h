@@ -139,8 +139,6 @@ struct JacArgs {
     // nothing once ctrl->done is set, and the persistent kernel raises
     // ctrl->sweep_max to each slice's sweep count
     Ctrl* ctrl;
-    int* clr[2];    // jacobi_init: optional int ranges zeroed before the sweeps
-    int nclr[2];
 };
 
 // C[s] = alpha * op(A[s]) * diag(d[s]) * op(B[s]) + beta * D[s] over `batch`
@@ -206,6 +204,14 @@ struct JacSliceArgs {
     double floor_scale;  // the rounding floor of rot_forces_sweep is floor_scale ||A||_F^2 (0: none)
     double* fro;         // pairs-parallel schedule with a floor: h x (nb / 2) doubles, the
                          // parts of the slices' squared Frobenius norms
+    // optional, with ctrl: after the sweeps, or where only_if left them out,
+    // `parts` workgroups a slice write the singular values and shrink factors
+    // of W (svt_sigma) and clear nclr words at clr except only_if's
+    double* sigma;
+    double* dk;
+    int parts;
+    int* clr;
+    int nclr;
 };
 // Doubles per problem of the pairs-parallel schedule's Frobenius parts (JacSliceArgs::fro).
 inline int64_t jacobi_pairs_fro(int h, int n) { return (int64_t)h * (n / 2 + 1); }
@@ -239,6 +245,24 @@ struct SigmaArgs {
     double* dk;         // shrink factors (1 - tau/sigma)_+, tau = ctrl->tau
     const Ctrl* ctrl;   // tau; skip the problem once done
 };
+// One wavefront: sigma = ||w|| of a column of m rows and its shrink factor
+// (1 - tau / sigma)_+; lanes stride the rows, FP64 accumulation, reduction with
+// cross-lane shuffles.
+template <typename T>
+__device__ __forceinline__ void sigma_column(const cplx<T>* w, int m, double tau, double* sigma, double* dk) {
+    const int lane = threadIdx.x & 63;
+    double acc = 0.0;
+    for (int r = lane; r < m; r += 64) {
+        const cplx<T> v = w[r];
+        acc += (double)v.re * v.re + (double)v.im * v.im;
+    }
+    for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
+    if (lane == 0) {
+        const double sg = sqrt(acc);
+        *sigma = sg;
+        *dk = sg > tau ? 1.0 - tau / sg : 0.0;
+    }
+}
 int svt_sigma_workgroups(int n, int h);
 template <typename T>
 void launch_svt_sigma_batched(const SigmaArgs<T>* tab, const int* wg_start, int nprob, int nwg, hipStream_t st);

@@ -6,8 +6,7 @@
 // sigma_j <= tau).  Both sigma and d are written here; the rebuild
 // Zhat = W diag(d) V^H is done by the matrix-core GEMM (zgemm.hip).
 //
-// One wavefront per column: lanes stride the m rows, FP64 accumulation,
-// reduction with cross-lane shuffles.  sigma is FP64 in both precision
+// One wavefront per column (sigma_column).  sigma is FP64 in both precision
 // forms (it decides which singular values survive the threshold).
 
 #include "kernels.h"
@@ -17,22 +16,10 @@ namespace tsvd {
 template <typename T>
 __device__ __forceinline__ void svt_sigma_body(const cplx<T>* W, int m, int n, int64_t cols, double* sigma,
                                                double* dk, double tau, int bid) {
-    const int lane = threadIdx.x & 63;
     const int64_t c = (int64_t)bid * (kBlock / 64) + (threadIdx.x >> 6);
     if (c >= cols) return;
     const int64_t s = c / n, j = c - s * n;
-    const cplx<T>* w = W + (s * n + j) * (int64_t)m;
-    double acc = 0.0;
-    for (int r = lane; r < m; r += 64) {
-        const cplx<T> v = w[r];
-        acc += (double)v.re * v.re + (double)v.im * v.im;
-    }
-    for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
-    if (lane == 0) {
-        const double sg = sqrt(acc);
-        sigma[c] = sg;
-        dk[c] = sg > tau ? 1.0 - tau / sg : 0.0;
-    }
+    sigma_column(W + (s * n + j) * (int64_t)m, m, tau, sigma + c, dk + c);
 }
 
 template <typename T>
