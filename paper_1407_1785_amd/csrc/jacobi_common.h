@@ -17,6 +17,24 @@ __device__ __forceinline__ int ppos_player(int pos, int r, int nb) {
     return pos == 0 ? 0 : 1 + (pos - 1 + r) % (nb - 1);
 }
 
+// Position, in global round R (counted over the sweeps, nb - 1 a sweep), of the
+// block in slot 0 of worker g of a slice; slot 1 holds the block at nb - 1
+// minus it.  Between rounds every block but the one at position 0 moves one
+// position down (from 1 to nb - 1), and one of the two positions of a pair is
+// even and one odd (nb - 1 is odd).  Instead of two blocks per worker on fixed
+// positions, the block at the even position stays with its worker, which takes
+// over that block's next pair, and only the block at the odd position goes to
+// another worker: half the traffic between rounds for the same pairs.  The
+// slots replace their block by turns (worker 0, which keeps block 0: slot 1).
+// An exchange is bound by the round trip through the coherence point and, with
+// two workgroups on every CU, by its rate (69 MB a round in 14 us for 33 slices
+// of 256 x 256).  Against two moving blocks: 256 x 256 x 64 FP32 RPCA 2.74 -> 2.43
+// ms an iteration, 128 x 160 x 64 completion 1.15 -> 1.05 ms in FP64 and 0.387 ->
+// 0.366 ms in FP32, a batch of uneven FP32 completions 346 -> 296 ms.
+__device__ __forceinline__ int ppos_slot0(int g, int R) {
+    return g == 0 || (R & 1) == 0 ? g : (g & 1 ? g + 1 : g - 1);
+}
+
 // DPP lane exchange within a 16-lane row.  Every lane reads a valid source
 // for the controls used here; with bound_ctrl the exchange folds into the
 // consuming add as a DPP source operand.

@@ -3,16 +3,14 @@
 // per-round kernels in jacobi.hip, which remain the path for shapes that do
 // not fit this one).
 //
-// Layout.  Slice s gets G = nb/2 workgroups; workgroup p holds the blocks at
-// tournament positions p (in registers) and nb-1-p (in LDS): two BW-column
-// blocks of stacked columns, m slice rows, then n rows of V.  A round of the
-// block tournament
-// orthogonalises the two resident blocks against each other; between rounds
-// every block except the one at position 0 moves to the next position
-// (circle method), so a workgroup writes its moving blocks back to their
-// home columns in global memory, meets the other workgroups of its slice at
-// a barrier, and reads the blocks of its next positions.  The first round of
-// every sweep also orthogonalises each block internally.  A slice of one
+// Layout.  Slice s gets G = nb/2 workgroups; a workgroup holds two BW-column
+// blocks of stacked columns (m slice rows, then n rows of V), one in registers
+// and one in LDS.  A round of the block tournament orthogonalises the two
+// against each other; between rounds one of them stays and the other goes to
+// another workgroup (ppos_slot0): the workgroup writes it back to its home
+// columns in global memory, sets its ready flag, and waits for the one block it
+// takes next.  The first round of every sweep also orthogonalises each block
+// internally.  A slice of one
 // block pair (n <= 32) shares no word with others and meets nobody: 32 x 32 x
 // 16 FP64 completion 152 -> 148 us an iteration.
 //
@@ -176,7 +174,6 @@ __global__ __launch_bounds__(PBW * PG) void jacobi_persistent_kernel(JacArgs<T> 
         slice_view(a.A + (int64_t)s * a.n * a.m, a.V + (int64_t)s * a.n * a.n, a.m, a.n, a.nb, ka, ldc);
     cplx<T>* const blk1 = reinterpret_cast<cplx<T>*>(smem);
     cplx<T> x[RPT];
-    const int pos0 = wg, pos1 = a.nb - 1 - wg;
     const int l = threadIdx.x % PG;
     const double tol = (double)a.tol;
     int* counter = p.pbar + s;
@@ -186,7 +183,7 @@ __global__ __launch_bounds__(PBW * PG) void jacobi_persistent_kernel(JacArgs<T> 
 
     if ((threadIdx.x & 63) == 0) wsteps[threadIdx.x >> 6] = 0;
     int steps = 0;   // pair steps finished by every wave before the current round
-    int player0 = ppos_player(pos0, 0, a.nb), player1 = ppos_player(pos1, 0, a.nb);
+    int player0 = ppos_player(wg, 0, a.nb), player1 = ppos_player(a.nb - 1 - wg, 0, a.nb);
     load_pair<T, PG, RPT, true>(sv, player0, x, player1, blk1);
     if (wg == 0 && threadIdx.x == 0) a.sweeps[s] = 0;
     __syncthreads();
@@ -245,7 +242,9 @@ __global__ __launch_bounds__(PBW * PG) void jacobi_persistent_kernel(JacArgs<T> 
             }
             // the next round's players (after the last round: round 0 of the next sweep)
             const int nr = (rd + 1) % (a.nb - 1);
-            const int next0 = ppos_player(pos0, nr, a.nb), next1 = ppos_player(pos1, nr, a.nb);
+            const int R = sweep * (a.nb - 1) + rd;
+            const int pos0 = ppos_slot0(wg, R + 1);
+            const int next0 = ppos_player(pos0, nr, a.nb), next1 = ppos_player(a.nb - 1 - pos0, nr, a.nb);
             if (next0 != player0) store_col<T, PG, RPT, true>(sv, player0, x);
             if (next1 != player1) store_lds<T, PG, RPT, true>(sv, player1, blk1);
             if (last) {
@@ -273,7 +272,6 @@ __global__ __launch_bounds__(PBW * PG) void jacobi_persistent_kernel(JacArgs<T> 
             } else {
                 // within a sweep: publish the blocks written (ready for round R + 1)
                 // and wait only for the two blocks this workgroup takes next
-                const int R = sweep * (a.nb - 1) + rd;
                 int* const bf = err + 2 + s * a.nb;
                 __builtin_amdgcn_s_waitcnt(0);
                 __syncthreads();

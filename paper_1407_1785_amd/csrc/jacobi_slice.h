@@ -86,7 +86,8 @@ __device__ __forceinline__ void slice_svd(const JacSliceArgs<T>& a, int s, int m
         unsigned nrot_sweep = 0, nbig_sweep = 0;
         for (int rd = 0; rd < nb - 1; ++rd) {
             for (int gp = 0; gp < G; ++gp) {
-                const int player0 = ppos_player(gp, rd, nb), player1 = ppos_player(nb - 1 - gp, rd, nb);
+                const int pos0 = ppos_slot0(gp, sweep * (nb - 1) + rd);
+                const int player0 = ppos_player(pos0, rd, nb), player1 = ppos_player(nb - 1 - pos0, rd, nb);
                 // (the round's own barriers end every use of the blocks it leaves behind)
                 if (G > 1) load_pair<T, PG, RPT, false>(sv, player0, x, player1, blk1);
                 __syncthreads();
@@ -156,11 +157,12 @@ void jacobi_slice_kernel(const JacSliceArgs<T>* tab, const int* wg_start, int np
 
 // Pairs-parallel schedule: nb / 2 workgroups per slice, one per block pair
 // of a round, all sweeps in one launch.  Workgroup roles (problem, slice,
-// block pair) come in order from words[0], as in jacobi_persist.hip, so the workgroups of a slice wait only
-// for workgroups that run or start as soon as others finish; between rounds
-// a workgroup writes the blocks that move to their home columns with
-// device-coherent stores, sets their ready flags to the round that takes them
-// next and waits for the flags of the blocks it takes next; at the end of a
+// block pair) come in order from words[0], as in jacobi_persist.hip, so the
+// workgroups of a slice wait only for workgroups that run or start as soon as
+// others finish; between rounds a workgroup writes the block that moves on
+// (ppos_slot0) to its home columns with device-coherent stores, sets its ready
+// flag to the round that takes it next and waits for the flag of the block it
+// takes next; at the end of a
 // sweep the slice's workgroups meet at a counter barrier and stop together
 // when no rotation of the sweep forces another.  Every wait between
 // workgroups is bounded (spin_limit polls); one that gives up sets words[1],
@@ -234,8 +236,7 @@ __global__ __launch_bounds__(BW * kPGs, (jacobi_waves_per_simd<T, kPGs, BW, RPT>
     __shared__ int wsteps[NT / 64];
     int steps = 0;
     if ((threadIdx.x & 63) == 0) wsteps[threadIdx.x >> 6] = 0;
-    const int pos0 = gp, pos1 = nb - 1 - gp;
-    int player0 = ppos_player(pos0, 0, nb), player1 = ppos_player(pos1, 0, nb);
+    int player0 = ppos_player(gp, 0, nb), player1 = ppos_player(nb - 1 - gp, 0, nb);
     load_pair<T, PG, RPT, true>(sv, player0, x, player1, blk1);
     __syncthreads();
 
@@ -283,7 +284,9 @@ __global__ __launch_bounds__(BW * kPGs, (jacobi_waves_per_simd<T, kPGs, BW, RPT>
             }
             // the next round's players (after the last round: round 0 of the next sweep)
             const int nr = (rd + 1) % (nb - 1);
-            const int next0 = ppos_player(pos0, nr, nb), next1 = ppos_player(pos1, nr, nb);
+            const int R = sweep * (nb - 1) + rd;
+            const int pos0 = ppos_slot0(gp, R + 1);
+            const int next0 = ppos_player(pos0, nr, nb), next1 = ppos_player(nb - 1 - pos0, nr, nb);
             if (next0 != player0) store_col<T, PG, RPT, true>(sv, player0, x);
             if (next1 != player1) store_lds<T, PG, RPT, true>(sv, player1, blk1);
             if (last) {
@@ -304,7 +307,6 @@ __global__ __launch_bounds__(BW * kPGs, (jacobi_waves_per_simd<T, kPGs, BW, RPT>
                     break;
                 }
             } else {
-                const int R = sweep * (nb - 1) + rd;
                 __builtin_amdgcn_s_waitcnt(0);
                 __syncthreads();
                 if (threadIdx.x == 0) {
