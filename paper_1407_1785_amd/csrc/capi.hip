@@ -51,7 +51,7 @@ struct SvtBuffers {
     int* rank;
     int* rot;
     int* sweeps;
-    int* pbar;        // persistent Jacobi: h barrier counters, 3h flags, the error word, the role
+    int* pbar;        // persistent Jacobi: h barrier words, the error word, the role
                       // ticket, h x nb block flags
     double* fro;      // persistent Jacobi: h x (nb / 2) parts of the slices' Frobenius norms
     double* partials;
@@ -64,8 +64,8 @@ struct SvtBuffers {
     int* fws;
 };
 
-// pbar words of a geometry: barriers, rotation flags, error word, ticket, block flags
-inline int64_t pbar_words(const Geometry& g) { return 4 * (int64_t)g.h + 2 + (int64_t)g.h * (g.n + 2); }
+// pbar words of a geometry: barriers, error word, ticket, block flags
+inline int64_t pbar_words(const Geometry& g) { return (int64_t)g.h + 2 + (int64_t)g.h * (g.n + 2); }
 // doubles of the per-workgroup Frobenius parts (at most n / 2 block pairs per slice)
 inline int64_t fro_doubles(const Geometry& g) { return (int64_t)g.h * (g.n / 2 + 1); }
 
@@ -228,10 +228,10 @@ constexpr double kGramFloor = 1.1920928955078125e-07 / 16;
 // SVD of a call (clear_persist_words) and again after every SVD.
 template <typename T>
 int persist_words(tsvd_handle h, const Geometry& g) {
-    if (gram_path<T>(h, g)) return 4 * g.h + 2 + g.h * jacobi_persistent_blocks(g.n);
+    if (gram_path<T>(h, g)) return g.h + 2 + g.h * jacobi_persistent_blocks(g.n);
     const JacPlan plan = jacobi_plan<T>(h, g);
-    if (plan.mode == JacMode::PERSIST) return 4 * g.h + 2 + g.h * jacobi_persistent_blocks(g.n);
-    return 4 * g.h + 1 + (plan.mode == JacMode::PAIRS ? g.h * (1 + plan.nb) : 0);
+    if (plan.mode == JacMode::PERSIST) return g.h + 2 + g.h * jacobi_persistent_blocks(g.n);
+    return g.h + 1 + (plan.mode == JacMode::PAIRS ? g.h * (1 + plan.nb) : 0);
 }
 
 // Workgroups that share a slice in the launch that ends an SVD: eight columns
@@ -256,12 +256,11 @@ void finish_args(tsvd_handle h, const Geometry& g, const SvtBuffers<T>& sb, JacS
 //  entries 0-3, the end of the SVD: the one-workgroup-per-slice kernel on the
 //  same slices (work buffer A or Z, V buffer 0 or 1), whose sweeps are the
 //  fallback after a persistent or block-pair launch that gave up, gated on the
-//  error word at pbar + 4h, and which writes the singular values;
+//  error word at pbar + h, and which writes the singular values;
 //  entries 4-7 (PAIRS only), the block-pair kernel on the same buffers.
 // In PAIRS mode the persistent kernel's int words hold the block-pair
-// kernel's: the rotation-flag ring at pbar, the role ticket at pbar + 4h - 1
-// and the error word at pbar + 4h (the fallback's gate), the barrier
-// counters and block flags from pbar + 4h + 1.
+// kernel's: the role ticket at pbar + h - 1 and the error word at pbar + h (the
+// fallback's gate), the barrier words and block flags from pbar + h + 1.
 template <typename T>
 void upload_fallback(tsvd_handle h, const Geometry& g, const SvtBuffers<T>& sb, int max_sweeps) {
     if (gram_path<T>(h, g)) {
@@ -279,7 +278,7 @@ void upload_fallback(tsvd_handle h, const Geometry& g, const SvtBuffers<T>& sb, 
         a.rotations = h->rot_counter + 1;
         a.max_sweeps = max_sweeps;
         a.floor_scale = kGramFloor * kGramFloor;
-        a.only_if = sb.pbar + 4 * g.h;
+        a.only_if = sb.pbar + g.h;
         finish_args(h, g, sb, a);
         const int ws[2] = {0, g.h * a.parts};
         char* stage = static_cast<char*>(ensure_host_stage(h, sizeof(a) + sizeof(ws)));
@@ -312,11 +311,10 @@ void upload_fallback(tsvd_handle h, const Geometry& g, const SvtBuffers<T>& sb, 
         a.max_sweeps = max_sweeps;
         a.floor_scale = jacobi_floor_scale(g.m, sizeof(T));
         if (k < 4) {
-            a.only_if = sb.pbar + 4 * g.h;
+            a.only_if = sb.pbar + g.h;
             finish_args(h, g, sb, a);
         } else {
-            a.rot = sb.pbar;
-            a.bar = sb.pbar + 4 * g.h + 1;
+            a.bar = sb.pbar + g.h + 1;
             a.fro = sb.fro;
         }
     }
@@ -728,7 +726,7 @@ SweepStats run_svt(tsvd_handle h, const Geometry& g, const SvtBuffers<T>& sb, in
         const int spin = std::max(0, env_int("TSVD_PERSIST_SPIN", 1 << 21));
         const int ip = prof_launch(h, K_JAC_PERSIST, 0.0, [&] {
             hip_check(launch_jacobi_pairs<T>(plan.bw, plan.rpt, sb.ftab + 4 + entry, sb.fws + 2, 1,
-                                             g.h * (plan.nb / 2), sb.pbar + 4 * g.h - 1, spin, st),
+                                             g.h * (plan.nb / 2), sb.pbar + g.h - 1, spin, st),
                       "jacobi block pairs");
         });
         done_persist = true;
@@ -932,7 +930,7 @@ LoopResult admm_loop(tsvd_handle h, int max_iter, F&& iteration) {
 void clear_flag(tsvd_handle h) { launch_fill<int>(h->flag, 0, 1, h->stream); }
 
 // Words of the one-launch Jacobi sweeps, cleared once per call (then by the end
-// of every SVD, but for the error word).  Error word, pbar[4h]: bit 1 (a wait
+// of every SVD, but for the error word).  Error word, pbar[h]: bit 1 (a wait
 // between workgroups gave up) only makes the fallback kernel finish the SVDs,
 // bit 2 (a wait inside a workgroup ran out: a fault) fails the call.
 template <typename T>
@@ -943,7 +941,7 @@ void clear_persist_words(tsvd_handle h, const Geometry& g, const SvtBuffers<T>& 
 template <typename T>
 void check_persist_err(tsvd_handle h, const Geometry& g, const SvtBuffers<T>& sb) {
     ensure_host_ints(h, 1);
-    hip_check(hipMemcpyAsync(h->host_ints, sb.pbar + 4 * g.h, sizeof(int), hipMemcpyDeviceToHost, h->stream),
+    hip_check(hipMemcpyAsync(h->host_ints, sb.pbar + g.h, sizeof(int), hipMemcpyDeviceToHost, h->stream),
               "hipMemcpyAsync err");
     hip_check(hipStreamSynchronize(h->stream), "hipStreamSynchronize");
     if (h->host_ints[0] & 2) fail(TSVD_E_HIP, "a Jacobi step wait inside a workgroup ran out");

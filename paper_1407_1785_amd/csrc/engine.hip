@@ -148,7 +148,6 @@ struct Slot {
     double* sigma = nullptr;
     double* dk = nullptr;       // shrink factors of the rebuild
     int* sweeps = nullptr;
-    int* rot = nullptr;         // pairs-parallel Jacobi: 3 x h rotation flags
     int* bar = nullptr;         // pairs-parallel Jacobi: barrier counters and block flags
     double* fro = nullptr;      // pairs-parallel Jacobi: parts of the slices' Frobenius norms
     double* partials = nullptr;
@@ -189,7 +188,6 @@ size_t slot_layout(Slot<T>& sl, char* base) {
     sl.sigma = reinterpret_cast<double*>(take((int64_t)g.h * g.n * sizeof(double)));
     sl.dk = reinterpret_cast<double*>(take((int64_t)g.h * g.n * sizeof(double)));
     sl.sweeps = reinterpret_cast<int*>(take((int64_t)g.h * sizeof(int)));
-    sl.rot = reinterpret_cast<int*>(take((int64_t)3 * g.h * sizeof(int)));
     // sized for the narrowest block width, the most blocks
     sl.bar = reinterpret_cast<int*>(take(jacobi_pairs_words(g.h, jacobi_num_blocks(g.n, 4)) * sizeof(int)));
     sl.fro = reinterpret_cast<double*>(take(jacobi_pairs_fro(g.h, g.n) * sizeof(double)));
@@ -457,7 +455,6 @@ private:
         for (int k = 0; k < nit; ++k) launch_fill<T>(sl.it[k][0], (T)0, N, st);
         launch_set_identity<T>(sl.V[0], g.n, g.h, st);
         launch_fill<int>(sl.flag, 0, 1, st);
-        launch_fill<int>(sl.rot, 0, 3 * g.h, st);
         launch_fill<int>(sl.bar, 0, jacobi_pairs_words(g.h, jacobi_num_blocks(g.n, 4)), st);
         launch_sumsq<T>(static_cast<const T*>(p.x), rpca ? nullptr : p.mask, N, sl.partials, 1024, st);
         launch_set_tol(sl.ctrl, sl.partials, 1024, p.tol, st);
@@ -498,7 +495,7 @@ private:
 
     // ---- Jacobi schedule tuner
     //
-    // Candidates: every block width whose two blocks fit in LDS, each with
+    // Candidates: every block width of which a block fits in LDS, each with
     // one workgroup per slice, and, where a slice has two or more block
     // pairs, one workgroup per block pair of a round.  One decision per
     // device, element type, row class, 32-column class and slice count
@@ -574,7 +571,7 @@ private:
     TuneChoice tune(int m, int n, int rpt, int S, const std::vector<TuneChoice>& cand) {
         const int64_t mn = (int64_t)m * n, nn = (int64_t)n * n;
         const int nb_max = jacobi_num_blocks(n, 4);
-        const size_t ints = 2 + 3 * (size_t)S + (size_t)jacobi_pairs_words(S, nb_max);
+        const size_t ints = 2 + (size_t)jacobi_pairs_words(S, nb_max);
         char* buf = nullptr;
         const size_t cbytes = sizeof(cplx<T>) * (size_t)S * (2 * mn + nn);
         hip_check(hipMalloc(&buf, cbytes + sizeof(int) * ints + 1024), "hipMalloc tuner");
@@ -582,8 +579,7 @@ private:
         cplx<T>* A = A0 + S * mn;
         cplx<T>* V = A + S * mn;
         int* words = reinterpret_cast<int*>(buf + cbytes);
-        int* rot = words + 2;
-        int* bar = rot + 3 * S;
+        int* bar = words + 2;
         JacSliceArgs<T>* dtab = nullptr;
         int* dws = nullptr;
         hip_check(hipMalloc(&dtab, sizeof(JacSliceArgs<T>)), "hipMalloc tuner");
@@ -605,7 +601,6 @@ private:
                 ja.nb = jacobi_num_blocks(n, c.bw);
                 ja.tol = (T)jacobi_tol(m, sizeof(T));
                 ja.max_sweeps = 1;
-                ja.rot = rot;
                 ja.bar = bar;
                 const int G = c.pairs ? ja.nb / 2 : 1;
                 const int ws[2] = {0, S * G};
@@ -792,7 +787,6 @@ private:
             ja.sweeps = sl.sweeps;
             ja.ctrl = sl.ctrl;
             ja.max_sweeps = sl.sp.s.max_sweeps;
-            ja.rot = sl.rot;
             ja.bar = sl.bar;
             ja.floor_scale = jacobi_floor_scale(g.m, sizeof(T));
             ja.fro = sl.fro;
@@ -842,8 +836,7 @@ private:
             inv.push_back(ia);
             ws_inv.push_back(ws_inv.back() + sl.inv_parts);
             lds_i = std::max(lds_i, dft_inverse_lds<T>(g, sl.tile_i, sl.epi));
-            ctl.push_back(CtrlArgs{sl.ctrl, sl.partials, sl.inv_parts, rpca ? 1 : 0, sl.pairs ? sl.rot : nullptr, g.h,
-                                   sl.pairs ? sl.bar : nullptr,
+            ctl.push_back(CtrlArgs{sl.ctrl, sl.partials, sl.inv_parts, rpca ? 1 : 0, sl.pairs ? sl.bar : nullptr,
                                    sl.pairs ? (int)jacobi_pairs_words(g.h, sl.nb) : 0});
         }
         auto put = [&](typename Tables<T>::Phase& ph, auto& args, std::vector<int>& ws, size_t lds) {

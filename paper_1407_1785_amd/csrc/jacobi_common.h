@@ -312,6 +312,43 @@ __device__ __forceinline__ unsigned ppair(cplx<T> (&x)[RPT], cplx<T>* y_lds, dou
     return code;
 }
 
+// The workgroups of a slice meet: 0 if the bounded wait ran out or another
+// workgroup gave up, 1 if all met and one of them voted (*vote, in LDS), 2 if
+// none did.  The blocks travel with device-coherent transfers, so no L2
+// write-back or invalidation is needed: every wave waits until its own stores
+// are complete at the coherence point, the workgroup meets, and thread 0 counts
+// the arrival (low half of the word) together with the vote (high half) and
+// waits for the others.  seen: the word at the last meeting (thread 0's); none
+// can arrive at the next one before all have left this one, since a sweep
+// needs every workgroup's blocks.  (Votes in a flag of their own, set before
+// and read after the meeting, cost two more
+// round trips: 0.8% of a video completion in FP32, 0.5% in FP64.)
+__device__ __forceinline__ int slice_meet(int* word, int G, const int* vote, unsigned& seen, int* err, int spin_limit) {
+    __shared__ int met;
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        __hip_atomic_fetch_add(word, vote && *vote ? 0x10001 : 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        int spins = 0;
+        met = 0;
+        for (;;) {
+            const unsigned v = (unsigned)__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (((v - seen) & 0xffff) >= (unsigned)G) {
+                met = (v ^ seen) >> 16 ? 1 : 2;
+                seen = v;
+                break;
+            }
+            __builtin_amdgcn_s_sleep(2);
+            if (__hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0 || ++spins > spin_limit) {
+                __hip_atomic_fetch_or(err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                break;
+            }
+        }
+    }
+    __syncthreads();
+    return met;
+}
+
 // Cross steps wave to wave: a wave finishes step st + 1 only after its
 // successor wave (cyclically) has finished step st, whose column it reads
 // next; each wave counts its finished steps in LDS (release after its LDS

@@ -26,9 +26,9 @@
 // coherent stores and loads.  Within a sweep, a workgroup that has written a
 // block waits for the stores to complete and then sets the block's flag to
 // the index of the round that takes it next; a workgroup waits only on the
-// flags of the two blocks it takes next.  At the end of a sweep all
-// workgroups of the slice meet at a counter barrier (the stopping decision
-// needs every workgroup's rotation flag).
+// flag of the block it takes next.  At the end of a sweep all workgroups of
+// the slice meet (slice_meet: the stopping decision needs every workgroup's
+// vote).
 //
 // Residency.  A workgroup takes its role (slice, block pair) from a ticket
 // counter when it starts, so the roles of the workgroups running at any time
@@ -44,10 +44,10 @@
 // together, so W = A V still holds for the partly rotated slices; the caller
 // then finishes the SVD with the one-workgroup-per-slice kernel.
 //
-// Convergence: workgroups OR a per-slice flag when a rotation of the sweep
-// forces another sweep (rot_forces_sweep); after the sweep's last barrier all
-// workgroups of the slice read the same flag and stop together when it is
-// clear.  The rounding floor of that test needs the slice's Frobenius norm:
+// Convergence: a workgroup votes for another sweep when a rotation of the
+// sweep forces one (rot_forces_sweep); the vote travels with its arrival at the
+// sweep's last barrier, and all workgroups of the slice stop together when
+// there is none.  The rounding floor of that test needs the slice's Frobenius norm:
 // each workgroup writes the part of its two starting blocks, and the
 // workgroups of a slice meet once before the first sweep, after which every
 // one adds the same parts in the same order.
@@ -63,38 +63,6 @@ namespace {
 using namespace jac;
 
 constexpr int PBW = 16;   // columns per block = pairs per step
-
-// Slice barrier: returns false if the bounded wait ran out.
-//
-// The blocks travel through global memory with device-coherent (relaxed
-// agent-scope atomic) loads and stores, so the barrier needs no L2
-// write-back or invalidation: every wave waits until its own stores are
-// complete at the coherence point, the workgroup meets at s_barrier, and
-// thread 0 counts the arrival and waits for the other workgroups of the
-// slice; the next blocks are read only after that (loads are issued in
-// program order).
-__device__ bool slice_barrier(int* counter, int target, int* err, int spin_limit) {
-    __shared__ int ok;
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        ok = 1;
-        __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        int spins = 0;
-        while (__hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
-            __builtin_amdgcn_s_sleep(2);
-            // another workgroup gave up: stop waiting at once
-            if (__hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0 ||
-                ++spins > spin_limit) {
-                __hip_atomic_fetch_or(err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                ok = 0;
-                break;
-            }
-        }
-    }
-    __syncthreads();
-    return ok != 0;
-}
 
 // Bounded wait (thread 0) until a block flag reaches `value`; false if the
 // wait ran out or another workgroup gave up.
@@ -149,17 +117,14 @@ __global__ __launch_bounds__(PBW * PG) void jacobi_persistent_kernel(JacArgs<T> 
     constexpr int NT = PBW * PG;
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ int rot_any;
-    __shared__ int stop;
     __shared__ int ok_flag;
     __shared__ double jnorm[PBW];
     __shared__ int wsteps[NT / 64];   // pair steps finished per wave, over the whole launch
     __shared__ int role;
     if (a.ctrl && a.ctrl->done) return;
     const int G = a.nb / 2;
-    // the int words of the launch: h barrier counters, 3h sweep flags, the
-    // error word, the role ticket, h x nb block flags
-    int* const rotflag = p.pbar + a.h;
-    int* const err = p.pbar + 4 * a.h;
+    // the int words of the launch: h barrier words, the error word, the role ticket, h x nb block flags
+    int* const err = p.pbar + a.h;
     if (threadIdx.x == 0) role = __hip_atomic_fetch_add(err + 1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
     // uniform across the workgroup: keep it (and what derives from it) scalar
@@ -177,7 +142,7 @@ __global__ __launch_bounds__(PBW * PG) void jacobi_persistent_kernel(JacArgs<T> 
     const int l = threadIdx.x % PG;
     const double tol = (double)a.tol;
     int* counter = p.pbar + s;
-    int arrivals = 0;
+    unsigned seen = 0;   // the barrier word at the last meeting (thread 0's)
     auto width = [&](int b) { return pblk_start(b + 1, a.n, a.nb) - pblk_start(b, a.n, a.nb); };
     auto wait = [&](const int* cnt, int value) { lds_wait(cnt, value, err); };
 
@@ -201,8 +166,7 @@ __global__ __launch_bounds__(PBW * PG) void jacobi_persistent_kernel(JacArgs<T> 
             pair_fro_part<T, PG, RPT, PBW>(x, blk1, width(player0), width(player1), ldc, ka, jnorm);
         if (G > 1) {
             if (threadIdx.x == 0) coh_store_f64(p.fro + (int64_t)s * G + wg, part);
-            arrivals += G;
-            alive = slice_barrier(counter, arrivals, err, p.spin_limit);
+            alive = slice_meet(counter, G, nullptr, seen, err, p.spin_limit) != 0;
         }
         if (G == 1) {
             floor2 = p.floor_scale * part;
@@ -220,9 +184,6 @@ __global__ __launch_bounds__(PBW * PG) void jacobi_persistent_kernel(JacArgs<T> 
     for (int sweep = 0; sweep < p.max_sweeps && alive; ++sweep) {
         if (threadIdx.x == 0) rot_any = 0;
         if (wg == 0 && threadIdx.x == 0) {
-            // read by every workgroup of the slice: a device-coherent store
-            __hip_atomic_store(rotflag + ((sweep + 1) % 3) * a.h + s, 0, __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
             a.sweeps[s] = sweep + 1;
             swept = sweep + 1;
         }
@@ -231,15 +192,8 @@ __global__ __launch_bounds__(PBW * PG) void jacobi_persistent_kernel(JacArgs<T> 
         for (int rd = 0; rd < a.nb - 1; ++rd) {
             nrot += pair_round<T, PG, PBW, RPT>(x, blk1, width(player0), width(player1), rd == 0, ka, ldc, tol, floor2,
                                                 jnorm, wsteps, steps, nbig, wait);
-            // end of the sweep: publish whether this workgroup needs another sweep
             const bool last = rd == a.nb - 2;
-            if (last) {
-                if (nbig && l == 0) rot_any = 1;
-                __syncthreads();
-                if (G > 1 && threadIdx.x == 0 && rot_any)
-                    __hip_atomic_fetch_or(rotflag + (sweep % 3) * a.h + s, 1, __ATOMIC_RELAXED,
-                                          __HIP_MEMORY_SCOPE_AGENT);
-            }
+            if (last && nbig && l == 0) rot_any = 1;   // this workgroup needs another sweep
             // the next round's players (after the last round: round 0 of the next sweep)
             const int nr = (rd + 1) % (a.nb - 1);
             const int R = sweep * (a.nb - 1) + rd;
@@ -248,30 +202,26 @@ __global__ __launch_bounds__(PBW * PG) void jacobi_persistent_kernel(JacArgs<T> 
             if (next0 != player0) store_col<T, PG, RPT, true>(sv, player0, x);
             if (next1 != player1) store_lds<T, PG, RPT, true>(sv, player1, blk1);
             if (last) {
-                // end of the sweep: every workgroup of the slice meets, then all
-                // read the same rotation flag and stop together when it is clear
-                // (a slice of one block pair asks its own flag: no word is shared)
-                arrivals += G;
-                if (G > 1 && !slice_barrier(counter, arrivals, err, p.spin_limit)) {
-                    home0 = next0 == player0;   // giving up
-                    home1 = next1 == player1;
-                    alive = false;
-                    break;
+                // end of the sweep: every workgroup of the slice meets, and all learn
+                // whether one needs another sweep (a slice of one block pair asks
+                // its own flag: no word is shared)
+                int met;
+                if (G > 1) {
+                    met = slice_meet(counter, G, &rot_any, seen, err, p.spin_limit);
+                } else {
+                    __syncthreads();
+                    met = rot_any ? 1 : 2;
+                    __syncthreads();
                 }
-                if (threadIdx.x == 0)
-                    stop = (G == 1 ? rot_any
-                                   : __hip_atomic_load(rotflag + (sweep % 3) * a.h + s, __ATOMIC_RELAXED,
-                                                       __HIP_MEMORY_SCOPE_AGENT)) == 0;
-                __syncthreads();
-                if (stop) {
-                    home0 = next0 == player0;   // converged
+                if (met != 1) {
+                    home0 = next0 == player0;   // giving up, or converged
                     home1 = next1 == player1;
                     alive = false;
                     break;
                 }
             } else {
-                // within a sweep: publish the blocks written (ready for round R + 1)
-                // and wait only for the two blocks this workgroup takes next
+                // within a sweep: publish the block written (ready for round R + 1)
+                // and wait only for the block this workgroup takes next
                 int* const bf = err + 2 + s * a.nb;
                 __builtin_amdgcn_s_waitcnt(0);
                 __syncthreads();

@@ -162,35 +162,14 @@ void jacobi_slice_kernel(const JacSliceArgs<T>* tab, const int* wg_start, int np
 // others finish; between rounds a workgroup writes the block that moves on
 // (ppos_slot0) to its home columns with device-coherent stores, sets its ready
 // flag to the round that takes it next and waits for the flag of the block it
-// takes next; at the end of a
-// sweep the slice's workgroups meet at a counter barrier and stop together
+// takes next; at the end of a sweep the slice's workgroups meet (slice_meet)
+// and stop together
 // when no rotation of the sweep forces another.  Every wait between
 // workgroups is bounded (spin_limit polls); one that gives up sets words[1],
 // and every workgroup that meets it writes its resident blocks home and
 // stops.  The rotations, their order and the stopping rule are those of the
 // one-workgroup-per-slice kernel (pair_round per block pair and round), so
 // both schedules give the same results bit for bit.
-__device__ bool pairs_barrier(int* counter, int target, int* err, int spin_limit) {
-    __shared__ int ok;
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        ok = 1;
-        __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        int spins = 0;
-        while (__hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
-            __builtin_amdgcn_s_sleep(2);
-            if (__hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0 || ++spins > spin_limit) {
-                __hip_atomic_fetch_or(err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                ok = 0;
-                break;
-            }
-        }
-    }
-    __syncthreads();
-    return ok != 0;
-}
-
 __device__ bool pairs_wait_flag(int* flag, int value, int* err, int spin_limit) {
     int spins = 0;
     while (__hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < value) {
@@ -208,7 +187,7 @@ __global__ __launch_bounds__(BW * kPGs, (jacobi_waves_per_simd<T, kPGs, BW, RPT>
                                                                   int nprob, int* words, int spin_limit) {
     constexpr int PG = kPGs, NT = BW * PG;
     extern __shared__ __align__(16) unsigned char smem[];
-    __shared__ int role_s, rot_any, stop, ok_flag;
+    __shared__ int role_s, rot_any, ok_flag;
     __shared__ double jnorm[BW];
     if (threadIdx.x == 0) role_s = __hip_atomic_fetch_add(words, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
@@ -221,7 +200,6 @@ __global__ __launch_bounds__(BW * kPGs, (jacobi_waves_per_simd<T, kPGs, BW, RPT>
     const int s = local / G, gp = local - s * G;
     int* const counter = a.bar + s;
     int* const bf = a.bar + h + (int64_t)s * nb;
-    int* const rot = a.rot;
     int* const err = words + 1;
     const int ka = (m + PG - 1) / PG;
     const int ldc = PG * RPT + 1;   // one more than the column: a wave's groups read different LDS banks
@@ -241,7 +219,8 @@ __global__ __launch_bounds__(BW * kPGs, (jacobi_waves_per_simd<T, kPGs, BW, RPT>
     __syncthreads();
 
     unsigned nrot = 0;
-    int sweeps = 0, arrivals = 0;
+    int sweeps = 0;
+    unsigned seen = 0;   // the barrier word at the last meeting (thread 0's)
     bool alive = true, home0 = true, home1 = true;
     // rounding floor of the stopping rule: every workgroup writes the part of
     // its round-0 block pair, the slice's workgroups meet once, and each adds
@@ -252,8 +231,7 @@ __global__ __launch_bounds__(BW * kPGs, (jacobi_waves_per_simd<T, kPGs, BW, RPT>
         const double part =
             pair_fro_part<T, PG, RPT, BW>(x, blk1, width(player0), width(player1), ldc, ka, jnorm);
         if (threadIdx.x == 0) coh_store_f64(a.fro + (int64_t)s * G + gp, part);
-        arrivals += G;
-        if (!pairs_barrier(counter, arrivals, err, spin_limit)) {
+        if (!slice_meet(counter, G, nullptr, seen, err, spin_limit)) {
             alive = false;   // giving up before any rotation: both blocks are still home
         } else {
             if (threadIdx.x == 0) {
@@ -267,8 +245,6 @@ __global__ __launch_bounds__(BW * kPGs, (jacobi_waves_per_simd<T, kPGs, BW, RPT>
     }
     for (int sweep = 0; sweep < msw && alive; ++sweep) {
         if (threadIdx.x == 0) rot_any = 0;
-        if (gp == 0 && threadIdx.x == 0)
-            __hip_atomic_store(rot + ((sweep + 1) % 3) * h + s, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         sweeps = sweep + 1;
         __syncthreads();
         unsigned nbig = 0;
@@ -276,12 +252,7 @@ __global__ __launch_bounds__(BW * kPGs, (jacobi_waves_per_simd<T, kPGs, BW, RPT>
             nrot += pair_round<T, PG, BW, RPT>(x, blk1, width(player0), width(player1), rd == 0, ka, ldc, tol, floor2,
                                                jnorm, wsteps, steps, nbig, ring_wait);
             const bool last = rd == nb - 2;
-            if (last) {
-                if (nbig && l == 0) rot_any = 1;
-                __syncthreads();
-                if (threadIdx.x == 0 && rot_any)
-                    __hip_atomic_fetch_or(rot + (sweep % 3) * h + s, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
+            if (last && nbig && l == 0) rot_any = 1;   // this workgroup needs another sweep
             // the next round's players (after the last round: round 0 of the next sweep)
             const int nr = (rd + 1) % (nb - 1);
             const int R = sweep * (nb - 1) + rd;
@@ -290,18 +261,8 @@ __global__ __launch_bounds__(BW * kPGs, (jacobi_waves_per_simd<T, kPGs, BW, RPT>
             if (next0 != player0) store_col<T, PG, RPT, true>(sv, player0, x);
             if (next1 != player1) store_lds<T, PG, RPT, true>(sv, player1, blk1);
             if (last) {
-                arrivals += G;
-                if (!pairs_barrier(counter, arrivals, err, spin_limit)) {
-                    home0 = next0 == player0;   // giving up
-                    home1 = next1 == player1;
-                    alive = false;
-                    break;
-                }
-                if (threadIdx.x == 0)
-                    stop = __hip_atomic_load(rot + (sweep % 3) * h + s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0;
-                __syncthreads();
-                if (stop) {
-                    home0 = next0 == player0;   // converged
+                if (slice_meet(counter, G, &rot_any, seen, err, spin_limit) != 1) {
+                    home0 = next0 == player0;   // giving up, or converged
                     home1 = next1 == player1;
                     alive = false;
                     break;

@@ -197,10 +197,9 @@ struct JacSliceArgs {
     Ctrl* ctrl;          // optional: skip the problem once ctrl->done; sweep_max is raised
     unsigned long long* rotations;  // optional running count
     int max_sweeps;      // sweep cap (0: the launch's)
-    int* rot;            // round mode: 3 x h ring of per-sweep rotation flags (ring 0 clear before the SVD)
     const int* only_if;  // optional: the problem is skipped unless *only_if != 0
-    int* bar;            // pairs-parallel schedule: h barrier counters, then h x nb block-ready
-                         // flags, all zero before the launch (as is ring 0 of rot)
+    int* bar;            // pairs-parallel schedule: h barrier words, then h x nb block-ready
+                         // flags, all zero before the launch
     double floor_scale;  // the rounding floor of rot_forces_sweep is floor_scale ||A||_F^2 (0: none)
     double* fro;         // pairs-parallel schedule with a floor: h x (nb / 2) doubles, the
                          // parts of the slices' squared Frobenius norms
@@ -336,8 +335,8 @@ void jacobi_set_lds_limit(size_t bytes);
 // Persistent Jacobi (jacobi_persist.hip): one launch per SVD.
 struct PersistArgs {
     int* pbar;        // int words, zero before the launch except the error word (zero
-                      // before the first launch of a call): h barrier counters, 3 x h
-                      // sweep flags, the error word (bit 1: a wait between workgroups
+                      // before the first launch of a call): h barrier words, the error
+                      // word (bit 1: a wait between workgroups
                       // gave up; bit 2: a wait inside one ran out), the role ticket,
                       // h x nb block-ready flags
     double* fro;      // h x (nb / 2) doubles: each workgroup's part of its slice's squared
@@ -357,8 +356,6 @@ struct CtrlArgs {
     Ctrl* c;
     const double* partials;
     int nparts, rpca;
-    int* rot_ring0;    // optional: h flags cleared after the step (pairs-parallel Jacobi)
-    int h;
     int* clr;          // optional: nclr ints cleared after the step (the Jacobi barrier area)
     int nclr;
 };
