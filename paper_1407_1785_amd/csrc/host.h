@@ -98,6 +98,7 @@ struct tsvd_handle_s {
     int host_ints_len = 0;
     void* host_stage = nullptr;     // argument tables uploaded once per call
     size_t host_stage_len = 0;
+    bool staged = false;   // a call has uploads from the pinned buffers that it has not waited for
     tsvd::Ctrl* host_ctrl = nullptr;
     // ADMM loop of the single-problem calls: the control kernel copies the
     // control block into one of two slots of mapped pinned host memory, and
