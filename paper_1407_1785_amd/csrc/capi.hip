@@ -494,6 +494,45 @@ int record_sweeps(tsvd_handle h, const Geometry& g, const SvtBuffers<T>& sb, int
     return smax;
 }
 
+// Sweeps of tall slices, columns in global memory, two launches per round;
+// returns the sweeps run.
+template <typename T>
+int tall_sweeps(tsvd_handle h, const Geometry& g, const SvtBuffers<T>& sb, JacArgs<T> ja, int max_sweeps) {
+    hipStream_t st = h->stream;
+    const TallPlan tp = jacobi_tall_plan(g.m, g.n, g.h);
+    const double pair_flops = 28.0 * g.m + 20.0 * g.n;
+    const int check_every = std::max(1, env_int("TSVD_CHECK_EVERY", 1));
+    int sweeps = 0;
+    ja.nb = tp.players;
+    prof_launch(h, K_JAC_INIT, (double)g.h * g.n * g.n * sizeof(cplx<T>), [&] { launch_jacobi_init(ja, st); });
+    launch_check("jacobi_init");
+    ja.rotations = h->rot_counter + 1;
+    for (int sw = 0; sw < max_sweeps; ++sw) {
+        ja.sweep = sw;
+        for (int r = 0; r < tp.players - 1; ++r) {
+            ja.round = r;
+            const int ip = prof_launch(h, K_JAC_CROSS, pair_flops * g.h * (tp.players / 2),
+                                       [&] { launch_jacobi_tall_round(ja, tp, sb.tall, st); });
+            if (ip >= 0) {
+                h->pending[ip].pairs = (double)g.h * (tp.players / 2);
+                if (r == 0) h->pending[ip].sweeps = g.h;
+            }
+            launch_check("jacobi_tall");
+        }
+        sweeps = sw + 1;
+        if (sweeps % check_every == 0 || sweeps == max_sweeps) {
+            hip_check(hipMemcpyAsync(h->host_ints, sb.rot + (sw % 3) * g.h, sizeof(int) * g.h, hipMemcpyDeviceToHost,
+                                     st),
+                      "hipMemcpyAsync rot");
+            hip_check(hipStreamSynchronize(st), "hipStreamSynchronize");
+            int active = 0;
+            for (int s = 0; s < g.h; ++s) active += h->host_ints[s] != 0;
+            if (!active) break;
+        }
+    }
+    return sweeps;
+}
+
 // C = alpha op(A) diag(dk) op(B) + beta D over square n x n slices (FP64).
 void square_gemm(tsvd_handle h, int kind, const Geometry& g, const cplx<double>* A, int opA, const cplx<double>* B,
                  int opB, cplx<double>* C, const double* dk = nullptr, const cplx<double>* D = nullptr,
@@ -598,6 +637,36 @@ SweepStats run_gram(tsvd_handle h, const Geometry& g, const SvtBuffers<float>& s
     stats.w = rebuild ? nullptr : sb.Z;
     stats.v = sb.V[vc];
     return stats;
+}
+
+// The Gram path's W = A V is one FP32 product, good for a thresholded sum
+// W diag(d) V^H, whose error it leaves at the rounding of A.  Divided by its
+// singular values it is not: every column carries about eps32 ||A|| of
+// rounding, and sigma is R V's, so the columns under 1e-7 of the first came
+// out with norms up to 1e32 (a slice of rank 3) and those at 1e-5 of it 7e-4
+// from orthogonal.  Sweeps of the global-memory Jacobi on (W, V) make the
+// columns orthogonal to kLeftTol of their own norms (the sums are in FP64, so
+// the bar needs no sqrt(m); it is far above what FP32 entries leave, 1e-7),
+// two or three from this start against seven to eight from V = I, and sigma
+// is their norm.
+constexpr double kLeftTol = 32 * 1.1920928955078125e-07;
+
+template <typename T>
+void left_vectors(tsvd_handle h, const Geometry& g, const SvtBuffers<T>& sb, const SweepStats& ss, int max_sweeps) {
+    JacArgs<T> ja{};
+    ja.A = static_cast<cplx<T>*>(const_cast<void*>(ss.w));
+    ja.V = static_cast<cplx<T>*>(const_cast<void*>(ss.v));
+    ja.m = g.m;
+    ja.n = g.n;
+    ja.h = g.h;
+    ja.rot = sb.rot;
+    ja.sweeps = sb.sweeps;
+    ja.tol = (T)kLeftTol;
+    ja.ctrl = h->ctrl;
+    tall_sweeps(h, g, sb, ja, max_sweeps);
+    prof_launch(h, K_SVT_W, (double)g.h * g.m * g.n * sizeof(cplx<T>) + (double)g.h * g.n * sizeof(double),
+                [&] { launch_svt_sigma(ja.A, g.m, g.n, g.h, sb.sigma, sb.dk, h->ctrl, h->stream); });
+    launch_check("svt_sigma");
 }
 
 // Jacobi sweeps + shrink + rebuild on the slices in sb.A; output in sb.Z.
@@ -746,36 +815,7 @@ SweepStats run_svt(tsvd_handle h, const Geometry& g, const SvtBuffers<T>& sb, in
         jac_ip = ip;
     }
     if (!done_persist && sb.tall) {
-        // tall slices: columns in global memory, two launches per round
-        const TallPlan tp = jacobi_tall_plan(g.m, g.n, g.h);
-        ja.nb = tp.players;
-        prof_launch(h, K_JAC_INIT, (double)g.h * g.n * g.n * sizeof(cplx<T>),
-                    [&] { launch_jacobi_init(ja, st); });
-        launch_check("jacobi_init");
-        ja.rotations = h->rot_counter + 1;
-        for (int sw = 0; sw < max_sweeps; ++sw) {
-            ja.sweep = sw;
-            for (int r = 0; r < tp.players - 1; ++r) {
-                ja.round = r;
-                const int ip = prof_launch(h, K_JAC_CROSS, pair_flops * g.h * (tp.players / 2),
-                                           [&] { launch_jacobi_tall_round(ja, tp, sb.tall, st); });
-                if (ip >= 0) {
-                    h->pending[ip].pairs = (double)g.h * (tp.players / 2);
-                    if (r == 0) h->pending[ip].sweeps = g.h;
-                }
-                launch_check("jacobi_tall");
-            }
-            stats.sweeps = sw + 1;
-            if ((sw + 1) % check_every == 0 || sw + 1 == max_sweeps) {
-                hip_check(hipMemcpyAsync(h->host_ints, sb.rot + (sw % 3) * g.h, sizeof(int) * g.h,
-                                         hipMemcpyDeviceToHost, st),
-                          "hipMemcpyAsync rot");
-                hip_check(hipStreamSynchronize(st), "hipStreamSynchronize");
-                int active = 0;
-                for (int s = 0; s < g.h; ++s) active += h->host_ints[s] != 0;
-                if (!active) break;
-            }
-        }
+        stats.sweeps = tall_sweeps(h, g, sb, ja, max_sweeps);
         done_persist = true;
     }
     if (!done_persist) {
@@ -1063,6 +1103,7 @@ void do_tsvt(tsvd_handle h, const void* X, tsvd_shape shape, tsvd_dtype dtype, d
 // forward DFT, cold Jacobi (up to 30 sweeps), singular values, and in 4-D
 // the conjugate pairs inside the half spectrum mirrored.  `extra` bytes of
 // workspace stay free after the SVD buffers for the caller's carver.
+// `divide`: the caller divides the columns of W by the singular values.
 template <typename T>
 struct SvdStage {
     SvtBuffers<T> sb;
@@ -1072,7 +1113,7 @@ struct SvdStage {
 };
 
 template <typename T>
-SvdStage<T> svd_stage(tsvd_handle h, const Geometry& g, const void* X, size_t extra) {
+SvdStage<T> svd_stage(tsvd_handle h, const Geometry& g, const void* X, size_t extra, bool divide) {
     const int nparts = (int)dft_grid(g, dft_inverse_tile(g, EPI_STORE));
     ensure_workspace(h, svt_bytes<T>(g, nparts) + extra + 4096);
     SvdStage<T> st;
@@ -1100,6 +1141,7 @@ SvdStage<T> svd_stage(tsvd_handle h, const Geometry& g, const void* X, size_t ex
                 [&] { launch_dft_forward(PRO_COPY, fa, h->stream); });
     launch_check("dft_forward");
     st.ss = run_svt<T>(h, g, st.sb, 30, nullptr, false, false);
+    if (divide && gram_path<T>(h, g)) left_vectors(h, g, st.sb, st.ss, 30);
     launch_tsvd_mirror<T>(static_cast<cplx<T>*>(const_cast<void*>(st.ss.w)),
                           static_cast<cplx<T>*>(const_cast<void*>(st.ss.v)), st.sb.sigma, g, h->stream);
     launch_check("tsvd_mirror");
@@ -1144,7 +1186,7 @@ void do_factors(tsvd_handle h, const void* M, tsvd_shape shape, void* U_out, voi
     Device dev(h->device);
     const int64_t n0 = g.n, n1 = g.n1, n2 = g.n2, hn = (int64_t)g.h * g.n;
     const size_t extra = hn * sizeof(int) + (size_t)g.h * (n1 + n2 + 1) * n0 * sizeof(cplx<T>) + 4 * 256;
-    SvdStage<T> st = svd_stage<T>(h, g, M, extra);
+    SvdStage<T> st = svd_stage<T>(h, g, M, extra, true);
     Carver cv = st.cv;
     int* rank = cv.take<int>(hn);
     cplx<T>* Uh = cv.take<cplx<T>>((int64_t)g.h * n1 * n0);
@@ -1178,7 +1220,7 @@ void do_compress(tsvd_handle h, const void* M, tsvd_shape shape, int32_t method,
     }
     Device dev(h->device);
     const int64_t hn = (int64_t)g.h * g.n;
-    SvdStage<T> st = svd_stage<T>(h, g, M, hn * sizeof(int) + 256);
+    SvdStage<T> st = svd_stage<T>(h, g, M, hn * sizeof(int) + 256, false);
     if (method == TSVD_COMPRESS_TUBAL) {
         Carver cv = st.cv;
         int* rank = cv.take<int>(hn);

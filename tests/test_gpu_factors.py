@@ -9,6 +9,7 @@ import numpy as np
 import pytest
 
 import paper_1407_1785_amd as lib
+from oracle import admm
 from oracle import compress as C
 from oracle import tensor as T
 from tests.gpu_util import announce, rel_fro, to_gpu, torch_cuda
@@ -88,6 +89,52 @@ def test_factors_fp32_form():
     assert orth_error(u) <= 1e-4 and orth_error(v) <= 1e-4
 
 
+def column_norm_error(f):
+    """Largest distance from 1 of a Fourier column's norm, columns that are
+    exactly zero left out."""
+    nrm = np.sqrt((np.abs(T.fourier(f)) ** 2).sum(axis=0))
+    return float(np.abs(nrm[nrm > 0] - 1).max())
+
+
+def spectrum(rng, kind, m, n, tube):
+    """Slices of rank 3, or with singular values from 1 down to `kind`."""
+    out = np.empty((m, n, tube))
+    for t in range(tube):
+        if kind == "rank3":
+            out[:, :, t] = rng.normal(size=(m, 3)) @ rng.normal(size=(3, n))
+        else:
+            u, _ = np.linalg.qr(rng.normal(size=(m, n)))
+            v, _ = np.linalg.qr(rng.normal(size=(n, n)))
+            out[:, :, t] = (u * np.geomspace(1.0, kind, n)) @ v.T * (1 + 0.2 * t)
+    return out
+
+
+@pytest.mark.parametrize("size", [(2000, 24, 1), (1152, 96, 1), (1500, 32, 3)])
+@pytest.mark.parametrize("kind", ["rank3", 1e-5, 1e-7])
+@pytest.mark.parametrize("wide", [False, True])
+def test_factors_tall_fp32(size, kind, wide):
+    """Tall slices in the FP32 form (the Gram path, csrc/tall.hip): the columns
+    of the divided factor are unit vectors and orthogonal, also those whose
+    singular values are at or under the rounding of the slice."""
+    torch = torch_cuda()
+    m = spectrum(np.random.default_rng(size[0] + 1), kind, *size).astype(np.float32)
+    if wide:
+        m = np.ascontiguousarray(m.transpose(1, 0, 2))
+    fourier_sv = np.linalg.svd(T.fourier(m).transpose(2, 0, 1), compute_uv=False)
+    tubes_ref = np.fft.ifft(fourier_sv, axis=0).real.T
+    announce("tsvd_factors tall fp32", m.shape, kind)
+    u, s, v = (t.cpu().numpy().astype(np.float64)
+               for t in lib.tsvd_factors(to_gpu(torch, m), precision=lib.PREC_FP32))
+    assert np.isfinite(u).all() and np.isfinite(v).all()
+    # FP32 norms of FP32 columns
+    assert column_norm_error(u) <= 1e-5 and column_norm_error(v) <= 1e-5
+    assert orth_error(u) <= 1e-4 and orth_error(v) <= 1e-4
+    # the singular values and the sum to the rounding of the FP32 rotations
+    # (some tens of units of 6e-8)
+    assert rel_fro(s, tubes_ref) <= 5e-6
+    assert rel_fro(reconstruct(u, s, v), m) <= 5e-6
+
+
 def test_factors_rank_deficient_slices():
     """A tubal-rank-2 tensor: the singular tubes beyond the second are zero
     and the reconstruction is still exact."""
@@ -165,6 +212,26 @@ def test_compression_fp32_form():
         announce("compress fp32", method, k)
         out, _ = lib.compress(mg, method, k, precision=lib.PREC_FP32)
         assert rel_fro(out.cpu().numpy().astype(np.float64), ref) <= TOL32
+
+
+@pytest.mark.parametrize("size", [(1500, 24, 1), (1100, 40, 3)])
+def test_tall_compression_and_rpca_fp32(size):
+    """Tall slices in the FP32 form: both compressions, also at a count that
+    keeps columns under the rounding of the slice, and a robust PCA."""
+    torch = torch_cuda()
+    m = spectrum(np.random.default_rng(size[1]), 1e-4, *size).astype(np.float32)
+    m64, mg = m.astype(np.float64), to_gpu(torch, m)
+    for method, k, ref in ((lib.COMPRESS_TUBAL, 7, C.method2), (lib.COMPRESS_TUBAL, size[1], C.method2),
+                           (lib.COMPRESS_TSVD, 10, C.method1)):
+        announce("compress tall fp32", size, method, k)
+        out, _ = lib.compress(mg, method, k, precision=lib.PREC_FP32)
+        assert rel_fro(out.cpu().numpy(), ref(m64, k)) <= 5e-6
+    lam = 1.0 / np.sqrt(max(size[:2]) * size[2])
+    announce("trpca tall fp32", size)
+    lo, sp, _ = lib.trpca(mg, lam, 1e-1, 0.0, max_iter=15, precision=lib.PREC_FP32)
+    want = admm.trpca(m64, lam, mu=1e-1, max_iter=15, tol=0.0)
+    assert rel_fro(lo.cpu().numpy(), want["L"]) <= TOL32
+    assert rel_fro(sp.cpu().numpy(), want["S"]) <= TOL32
 
 
 def test_compression_errors():
