@@ -107,7 +107,7 @@ struct Rot {
 __device__ __forceinline__ bool make_rotation(double al, double be, double gr, double gi, double tol,
                                               Rot& r) {
     const double g2 = gr * gr + gi * gi;
-    if (!(g2 > (tol * tol) * al * be) || !(g2 > 0.0)) return false;
+    if (!(g2 > (tol * tol) * al * be) || !(g2 > kMinGamma2)) return false;
     r.big = rot_forces_sweep(al, be, g2, tol);
     const double rg = rsqrt_acc(g2);
     const double zeta = (be - al) * 0.5 * rg;

@@ -138,9 +138,9 @@ struct PRot {
     bool on;
 };
 
-// The pair is rotated when |gamma|^2 > tol^2 alpha beta (and gamma != 0).
+// The pair is rotated when |gamma|^2 > tol^2 alpha beta (and kMinGamma2).
 __device__ __forceinline__ bool prot_needed(double al, double be, double g2, double tol) {
-    return g2 > (tol * tol) * al * be && g2 > 0.0;
+    return g2 > (tol * tol) * al * be && g2 > kMinGamma2;
 }
 
 // The rotation through d = beta - alpha and r = sqrt(d^2 + 4 |gamma|^2)

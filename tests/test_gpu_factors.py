@@ -148,6 +148,24 @@ def test_factors_rank_deficient_slices():
     assert rel_fro(reconstruct(u, s, v), m) <= TOL
 
 
+@pytest.mark.parametrize("size", [(96, 96, 3), (160, 128, 2), (40, 24, 1), (1500, 30, 1)])
+@pytest.mark.parametrize("fp32", [False, True])
+def test_factors_exact_null_space(size, fp32):
+    """Three nonzero rows: the columns of a slice lie in a space of three
+    dimensions exactly, and those that the rotations empty shrink by the
+    rounding unit sweep after sweep, down to where products of their squared
+    norms underflow.  V stays unitary (100 n units of the type)."""
+    torch = torch_cuda()
+    dt, prec, eps = (np.float32, lib.PREC_FP32, 1.2e-7) if fp32 else (np.float64, lib.PREC_FP64, 2.2e-16)
+    for seed in range(4):
+        rng = np.random.default_rng(seed)
+        m = np.zeros(size, dtype=dt)
+        m[[1, 7, size[0] - 2]] = rng.normal(size=(3,) + size[1:])
+        announce("tsvd_factors null space", size, fp32, seed)
+        v = lib.tsvd_factors(to_gpu(torch, m), precision=prec)[2].cpu().numpy().astype(np.float64)
+        assert orth_error(v) <= 100 * size[1] * eps, seed
+
+
 # ------------------------------------------------------------ compression
 
 COMPRESS_SHAPES = [(20, 13, 7), (13, 20, 8), (32, 32, 16), (40, 33, 1), (70, 45, 5)]
