@@ -108,10 +108,12 @@ __device__ __forceinline__ bool make_rotation(double al, double be, double gr, d
                                               Rot& r) {
     const double g2 = gr * gr + gi * gi;
     if (!(g2 > (tol * tol) * al * be) || !(g2 > kMinGamma2)) return false;
-    r.big = rot_forces_sweep(al, be, g2, tol);
     const double rg = rsqrt_acc(g2);
     const double zeta = (be - al) * 0.5 * rg;
     const double az = fabs(zeta);
+    // zeta^2 would overflow: a column whose part along the other is under
+    // 1e-150 of it (tall slices of exact rank below n) stays as it is
+    if (!(az < 1e150)) return false;
     const double q = 1.0 + zeta * zeta;
     const double t = rcp_close(az + q * rsqrt_acc(q));
     const double ts = zeta >= 0.0 ? t : -t;
@@ -119,6 +121,7 @@ __device__ __forceinline__ bool make_rotation(double al, double be, double gr, d
     r.s = r.c * ts;
     r.er = gr * rg;
     r.ei = gi * rg;
+    r.big = rot_forces_sweep(al, be, g2, tol);
     return true;
 }
 

@@ -162,8 +162,9 @@ def test_factors_exact_null_space(size, fp32):
         m = np.zeros(size, dtype=dt)
         m[[1, 7, size[0] - 2]] = rng.normal(size=(3,) + size[1:])
         announce("tsvd_factors null space", size, fp32, seed)
-        v = lib.tsvd_factors(to_gpu(torch, m), precision=prec)[2].cpu().numpy().astype(np.float64)
+        u, s, v = (t.cpu().numpy().astype(np.float64) for t in lib.tsvd_factors(to_gpu(torch, m), precision=prec))
         assert orth_error(v) <= 100 * size[1] * eps, seed
+        assert fp32 or rel_fro(reconstruct(u, s, v), m) <= 100 * size[1] * eps, seed
 
 
 # ------------------------------------------------------------ compression
