@@ -71,7 +71,11 @@ __global__ __launch_bounds__(kBlock) void tsvd_rank_kernel(const double* sigma, 
 }
 
 // Uhat, Vhat, Shat of every slice, columns in rank order; a column with
-// sigma = 0 gets a zero left singular vector.
+// sigma = 0, or under the smallest normal number (1 / sigma overflows, the
+// column has no digits left), gets a zero left singular vector.
+template <typename T>
+constexpr double kMinSigma = sizeof(T) == 4 ? 1.1754943508222875e-38 : 2.2250738585072014e-308;
+
 template <typename T>
 __global__ __launch_bounds__(kBlock) void tsvd_factor_kernel(const cplx<T>* W, const cplx<T>* V, const double* sigma,
                                                             const int* rank, Geometry g, cplx<T>* Uh, cplx<T>* Vh,
@@ -88,7 +92,7 @@ __global__ __launch_bounds__(kBlock) void tsvd_factor_kernel(const cplx<T>* W, c
             const double sg = sigma[(int64_t)s * n + j];
             const int r = rank[(int64_t)s * n + j];
             const cplx<T> w = W[s * mn + i];
-            const T f = sg > 0.0 ? (T)(1.0 / sg) : (T)0;
+            const T f = sg >= kMinSigma<T> ? (T)(1.0 / sg) : (T)0;
             if (g.trans)
                 Vh[(int64_t)s * n2 * n + (int64_t)r * n2 + row] = cplx<T>{w.re * f, -w.im * f};
             else
