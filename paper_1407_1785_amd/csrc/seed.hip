@@ -129,12 +129,22 @@ template <int R, int S>
 struct SeedState {
     Z2 x[S][R];        // the lane row's columns of A^H
     double cn[S];      // remaining squared norms (elements >= step); < 0 once taken
-    float cref[S];     // their value when last computed from the column
+    float cref[S];     // their value when last computed from the column, over the power of two of ||A||_F^2
+};
+
+// A remaining norm is recomputed from its column under 1e-6 of its last
+// computed value.  Those are kept in FP32 relative to the power of two next to
+// ||A||_F^2, so that the steps are the same at every scale of the data (as they
+// come they are 0 for entries under 1e-23, where no norm would be recomputed,
+// and infinite over 1e19, where every one would at every step).
+struct SeedScale {
+    double inv;   // over the power of two
+    double lim;   // 1e-6 times it
 };
 
 // Steps j >= 16 K0; returns the steps done.
 template <int R, int S, int K0>
-__device__ __forceinline__ int seed_steps(SeedState<R, S>& st, SeedShared& sh, int n, double stop2,
+__device__ __forceinline__ int seed_steps(SeedState<R, S>& st, SeedShared& sh, int n, double stop2, SeedScale sc,
                                           cplx<double>* G) {
     const int lane = threadIdx.x & 63, l = lane & 15, row = threadIdx.x >> 4;
     const int j1 = min(16 * (K0 + 1), n);
@@ -212,11 +222,11 @@ __device__ __forceinline__ int seed_steps(SeedState<R, S>& st, SeedShared& sh, i
             const double t = st.x[i][K0].re * st.x[i][K0].re + st.x[i][K0].im * st.x[i][K0].im;
             double c = st.cn[i];
             if (c > 0.0) c = fmax(c - __shfl(t, (lane & 48) | jl), 0.0);
-            if (__any(c >= 0.0 && c < 1e-6 * st.cref[i])) {
+            if (__any(c >= 0.0 && c < sc.lim * st.cref[i])) {
                 const double nn = tail_norm2<R, K0>(st.x[i], l, j + 1);
                 if (c >= 0.0) {
                     c = nn;
-                    st.cref[i] = (float)nn;
+                    st.cref[i] = (float)(sc.inv * nn);
                 }
             }
             st.cn[i] = c;
@@ -226,10 +236,11 @@ __device__ __forceinline__ int seed_steps(SeedState<R, S>& st, SeedShared& sh, i
 }
 
 template <int R, int S, int K0 = 0>
-__device__ __forceinline__ int seed_all(SeedState<R, S>& st, SeedShared& sh, int n, double stop2, cplx<double>* G) {
-    const int d = seed_steps<R, S, K0>(st, sh, n, stop2, G);
+__device__ __forceinline__ int seed_all(SeedState<R, S>& st, SeedShared& sh, int n, double stop2, SeedScale sc,
+                                        cplx<double>* G) {
+    const int d = seed_steps<R, S, K0>(st, sh, n, stop2, sc, G);
     if (d >= 0 || n <= 16 * (K0 + 1)) return d < 0 ? n : d;
-    if constexpr (K0 + 1 < R) return seed_all<R, S, K0 + 1>(st, sh, n, stop2, G);
+    if constexpr (K0 + 1 < R) return seed_all<R, S, K0 + 1>(st, sh, n, stop2, sc, G);
     return n;
 }
 
@@ -290,13 +301,16 @@ __global__ __launch_bounds__(kSeedThreads) void jacobi_seed_kernel(const cplx<do
             const double nn = tail_norm2<R, 0>(st.x[i], l, 0);
             part += nn;
             st.cn[i] = c < m ? nn : -1.0;
-            st.cref[i] = (float)nn;
         }
         if (l == 0) fro[row] = part;
         __syncthreads();
         double f2 = 0.0;
         for (int w = 0; w < kSeedRows; ++w) f2 += fro[w];
-        done = seed_all<R, S>(st, sh, n, fmax(4.93e-32 * f2, kSeedTiny), g);   // eps^2 ||A||_F^2
+        const int e = f2 > kSeedTiny ? ilogb(f2) : 0;
+        const SeedScale sc{ldexp(1.0, -e), ldexp(1e-6, e)};
+#pragma unroll
+        for (int i = 0; i < S; ++i) st.cref[i] = (float)(sc.inv * st.cn[i]);
+        done = seed_all<R, S>(st, sh, n, fmax(4.93e-32 * f2, kSeedTiny), sc, g);   // eps^2 ||A||_F^2
     }
     __syncthreads();   // the reflectors of every wave are in memory
     constexpr int QS = (16 * R + kSeedRows - 1) / kSeedRows;

@@ -80,3 +80,21 @@ def test_seed_saves_sweeps(monkeypatch):
         h.close()
     assert rel_fro(out[0], out[1]) <= TOL
     assert sweeps[0] < 0.5 * sweeps[1], sweeps
+
+
+@pytest.mark.parametrize("power", [-100, 83])
+def test_seed_at_every_scale(power):
+    """Data scaled by a power of two take the same steps and sweeps, also where
+    their squared norms leave the FP32 range."""
+    torch = torch_cuda()
+    x = smooth(np.random.default_rng(9), 96, 80, 6)
+    out, sweeps = [], []
+    for scale in (1.0, 2.0 ** power):
+        h = lib.Handle(0)
+        h.profile(True)
+        announce("seed scale sweeps", scale)
+        out.append(lib.tsvt(to_gpu(torch, x * scale), 0.5 * scale, handle=h)[0].cpu().numpy() / scale)
+        sweeps.append(h.profile_read()["jacobi_persistent"]["slice_sweeps"])
+        h.close()
+    assert sweeps[0] == sweeps[1]
+    np.testing.assert_array_equal(out[0], out[1])
