@@ -194,7 +194,10 @@ JacPlan jacobi_plan(tsvd_handle h, const Geometry& g) {
     for (int bw : {16, 8, 4}) {
         if (jacobi_slice_lds(bw, p.rpt, sizeof(T)) + 256 > h->lds_cap) continue;
         const int nb = jacobi_num_blocks(g.n, bw);
-        if (nb / 2 < 2) break;   // one block pair per slice: nothing to run in parallel
+        // one block pair per slice leaves nothing to run in parallel: narrower
+        // blocks make more of it (FP64 t-SVT in rounds, in block pairs: 560 x 32 x
+        // 64 1.65, 0.64 ms; 500 x 20 0.85, 0.48 ms; 300 x 12 x 512 0.89, 0.56 ms)
+        if (nb / 2 < 2) continue;
         p.mode = JacMode::PAIRS;
         p.bw = bw;
         p.nb = nb;

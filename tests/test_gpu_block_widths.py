@@ -10,6 +10,7 @@ import pytest
 
 import paper_1407_1785_amd as lib
 from oracle import admm
+from oracle.tsvt import tsvt as tsvt_oracle
 from tests.gpu_util import announce, rel_fro, to_gpu, torch_cuda
 
 pytestmark = pytest.mark.gpu
@@ -45,3 +46,21 @@ def test_narrow_blocks(monkeypatch, n, batch):
         out.append(p.out.cpu().numpy())
         assert rel_fro(out[-1], ref) <= 1e-10
     np.testing.assert_array_equal(out[0], out[1])
+
+
+@pytest.mark.parametrize("size", [(500, 20, 2), (560, 32, 2), (600, 12, 2), (545, 9, 2), (600, 17, 2)])
+def test_few_columns_many_rows(size):
+    """One block pair of 16 columns a slice, too many rows for the persistent
+    kernel (17 to 20 row groups in FP64): narrower blocks, in one launch."""
+    torch = torch_cuda()
+    x = np.random.default_rng(size[0]).normal(size=size)
+    tau = 0.7 * np.sqrt(size[0])
+    h = lib.Handle(0)
+    h.profile(True)
+    announce("few columns", size)
+    z, ranks = lib.tsvt(to_gpu(torch, x), tau, handle=h)
+    kinds = h.profile_read()
+    h.close()
+    ref, rank_ref = tsvt_oracle(x, tau)
+    assert rel_fro(z.cpu().numpy(), ref) <= 1e-12 and ranks == list(rank_ref)
+    assert "jacobi_persistent" in kinds and "jacobi_cross" not in kinds
