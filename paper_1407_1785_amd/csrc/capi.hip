@@ -475,6 +475,26 @@ struct SweepStats {
     const void* v = nullptr;     // V
 };
 
+// The persistent Jacobi launch.  False, with no timing record left in ip, where
+// the occupancy found at the launch does not hold its grid.
+// TSVD_PERSIST_CUS lowers the number of CUs it counts on (tests of that).
+template <typename E>
+bool run_persistent(tsvd_handle h, const JacArgs<E>& ja, const PersistArgs& pa, int& ip) {
+    hipError_t e = hipSuccess;
+    ip = prof_launch(h, K_JAC_PERSIST, 0.0,
+                     [&] { e = launch_jacobi_persistent(ja, pa, env_int("TSVD_PERSIST_CUS", h->cus), h->stream); });
+    if (e == hipSuccess) return true;
+    (void)hipGetLastError();
+    if (ip >= 0) {
+        // the timing events bracket nothing; drop the record
+        h->ev_pool.push_back(h->pending[ip].a);
+        h->ev_pool.push_back(h->pending[ip].b);
+        h->pending.erase(h->pending.begin() + ip);
+        ip = -1;
+    }
+    return false;
+}
+
 // Profiling: the sweeps of a one-launch SVD, read back into pending record ip
 // (n(n-1)/2 visited pairs per slice per sweep run); returns the largest.
 template <typename T>
@@ -592,9 +612,10 @@ SweepStats run_gram(tsvd_handle h, const Geometry& g, const SvtBuffers<float>& s
     pa.floor_scale = kGramFloor * kGramFloor;
     pa.max_sweeps = max_sweeps;
     pa.spin_limit = std::max(0, env_int("TSVD_PERSIST_SPIN", 1 << 21));
-    const int ip = prof_launch(h, K_JAC_PERSIST, 0.0, [&] {
-        hip_check(launch_jacobi_persistent(ja, pa, h->cus, st), "jacobi_persistent");
-    });
+    int ip = -1;
+    // a refused launch is one whose first wait gave up: the launch that ends the
+    // SVD runs its sweeps
+    if (!run_persistent(h, ja, pa, ip)) launch_fill<int>(sb.pbar + g.h, 1, 1, st);
     SweepStats stats;
     stats.sweeps = -1;   // known on the device only
     stats.on_device = true;
@@ -785,22 +806,10 @@ SweepStats run_svt(tsvd_handle h, const Geometry& g, const SvtBuffers<T>& sb, in
         // about a second of polling; TSVD_PERSIST_SPIN lowers it (tests of the fallback)
         pa.spin_limit = std::max(0, env_int("TSVD_PERSIST_SPIN", 1 << 21));
         pa.spread = env_int("TSVD_SPREAD", 0);
-        hipError_t e = hipSuccess;
-        const int ip = prof_launch(h, K_JAC_PERSIST, 0.0,
-                                   [&] { e = launch_jacobi_persistent(ja, pa, h->cus, st); });
-        if (e == hipSuccess) {
+        if (run_persistent(h, ja, pa, jac_ip)) {
             done_persist = true;
             stats.sweeps = -1;   // known on the device only
             stats.on_device = true;
-            jac_ip = ip;
-        } else {
-            (void)hipGetLastError();
-            if (ip >= 0) {
-                // the timing events bracket nothing; drop the record
-                h->ev_pool.push_back(h->pending[ip].a);
-                h->ev_pool.push_back(h->pending[ip].b);
-                h->pending.erase(h->pending.begin() + ip);
-            }
         }
     }
     if (plan.mode == JacMode::PAIRS) {

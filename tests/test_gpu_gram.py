@@ -78,6 +78,31 @@ def test_gram_completion_warm_and_cold(monkeypatch):
     assert_close_fp32(solve(max_iter=12), ref, 1e-4, "global-memory Jacobi")
 
 
+@pytest.mark.parametrize("size", [(1400, 40, 1), (1100, 33, 3), (48, 40, 6)])
+def test_refused_persistent_launch(monkeypatch, size):
+    """A card that does not hold the persistent Jacobi's grid: the SVDs of the
+    Gram path and of the ordinary one finish by another kernel."""
+    torch = torch_cuda()
+    m, n, tube = size
+    rng = np.random.default_rng(m)
+    x = np.stack([graded(rng, m, n, 1e-4) * (1 + t) for t in range(tube)], axis=2).astype(np.float32)
+    tau = float(0.5 * np.linalg.svd(x.sum(axis=2), compute_uv=False)[n // 4])
+    mask = (rng.random(x.shape) < 0.5).astype(np.uint8)
+    monkeypatch.setenv("TSVD_PERSIST_CUS", "0")
+    announce("refused launch", size)
+    h = lib.Handle(0)
+    for prof in (False, True):
+        h.profile(prof)
+        z, _ = lib.tsvt(to_gpu(torch, x), tau, lib.PREC_FP32, handle=h)
+        err = rel_fro(z.cpu().numpy(), tsvt_oracle(x, tau)[0])
+        assert err <= (TOL_GRAM if m > 1000 else 1e-4)   # or the FP32 rotations' own bar
+    out = lib.tsvd_complete(to_gpu(torch, x * mask), to_gpu(torch, mask), 1e-2, 0.0, max_iter=6,
+                            precision=lib.PREC_FP32, handle=h)[0]
+    h.close()
+    assert_close_fp32(out.cpu().numpy(), admm.complete(x * mask, mask, max_iter=6, tol=0.0)["X"], 1e-4,
+                      "refused launch")
+
+
 @pytest.mark.parametrize("shape", [(65, 63, 1), (63, 130, 1), (64, 64, 1), (3, 200, 1)])
 @pytest.mark.parametrize("fp32", [False, True])
 def test_matrix_transforms(shape, fp32):
