@@ -517,6 +517,20 @@ int record_sweeps(tsvd_handle h, const Geometry& g, const SvtBuffers<T>& sb, int
     return smax;
 }
 
+// Profiling: the rotations counted on the device since the last SVD (the second
+// count is `kind`'s), with the launches' times.
+void record_rotations(tsvd_handle h, int kind) {
+    unsigned long long rots[2] = {0, 0};
+    hip_check(hipMemcpyAsync(rots, h->rot_counter, sizeof(rots), hipMemcpyDeviceToHost, h->stream),
+              "hipMemcpyAsync rotations");
+    hip_check(hipStreamSynchronize(h->stream), "hipStreamSynchronize");
+    hip_check(hipMemsetAsync(h->rot_counter, 0, 2 * sizeof(unsigned long long), h->stream),
+              "hipMemsetAsync rotations");
+    prof_harvest(h);
+    h->agg[K_JAC_SELF].rotations += (double)rots[0];
+    h->agg[kind].rotations += (double)rots[1];
+}
+
 // Sweeps of tall slices, columns in global memory, two launches per round;
 // returns the sweeps run.
 template <typename T>
@@ -652,7 +666,7 @@ SweepStats run_gram(tsvd_handle h, const Geometry& g, const SvtBuffers<float>& s
         hip_check(hipStreamSynchronize(st), "hipStreamSynchronize");
         for (int s = 0; s < g.h; ++s) h->pending[ir].kept += h->host_ints[s];
     }
-    if (h->prof_on) prof_harvest(h);
+    if (h->prof_on) record_rotations(h, K_JAC_PERSIST);
     if (warm) {
         warm->valid = true;
         warm->iter += 1;
@@ -688,6 +702,7 @@ void left_vectors(tsvd_handle h, const Geometry& g, const SvtBuffers<T>& sb, con
     ja.tol = (T)kLeftTol;
     ja.ctrl = h->ctrl;
     tall_sweeps(h, g, sb, ja, max_sweeps);
+    if (h->prof_on) record_rotations(h, K_JAC_CROSS);
     prof_launch(h, K_SVT_W, (double)g.h * g.m * g.n * sizeof(cplx<T>) + (double)g.h * g.n * sizeof(double),
                 [&] { launch_svt_sigma(ja.A, g.m, g.n, g.h, sb.sigma, sb.dk, h->ctrl, h->stream); });
     launch_check("svt_sigma");
@@ -906,18 +921,7 @@ SweepStats run_svt(tsvd_handle h, const Geometry& g, const SvtBuffers<T>& sb, in
         launch_multirank(sb.sigma, g.n, g.n, g.h, h->ctrl, sb.rank, st);
         launch_check("multirank");
     }
-    if (h->prof_on) {
-        // rotation work needs the device counts
-        unsigned long long rots[2] = {0, 0};
-        hip_check(hipMemcpyAsync(rots, h->rot_counter, sizeof(rots), hipMemcpyDeviceToHost, st),
-                  "hipMemcpyAsync rotations");
-        hip_check(hipStreamSynchronize(st), "hipStreamSynchronize");
-        hip_check(hipMemsetAsync(h->rot_counter, 0, 2 * sizeof(unsigned long long), st),
-                  "hipMemsetAsync rotations");
-        prof_harvest(h);
-        h->agg[K_JAC_SELF].rotations += (double)rots[0];
-        h->agg[done_persist ? K_JAC_PERSIST : K_JAC_CROSS].rotations += (double)rots[1];
-    }
+    if (h->prof_on) record_rotations(h, done_persist ? K_JAC_PERSIST : K_JAC_CROSS);
     if (warm) {
         warm->valid = true;
         warm->iter += 1;

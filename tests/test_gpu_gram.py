@@ -103,6 +103,23 @@ def test_refused_persistent_launch(monkeypatch, size):
                       "refused launch")
 
 
+def test_gram_profile_counts_rotations():
+    """The profile of a Gram-path call has its rotations, and leaves none to the
+    next call's."""
+    torch = torch_cuda()
+    rng = np.random.default_rng(2)
+    h = lib.Handle(0)
+    h.profile(True)
+    announce("gram profile")
+    lib.tsvt(to_gpu(torch, graded(rng, 1200, 24)[:, :, None].astype(np.float32)), 1e-3, lib.PREC_FP32, handle=h)
+    k = h.profile_read()["jacobi_persistent"]
+    assert 0 < k["rotations"] <= k["pairs_visited"]
+    before = k["rotations"]
+    lib.tsvt(to_gpu(torch, np.zeros((32, 32, 1))), 0.5, handle=h)   # rotates nothing
+    assert h.profile_read()["jacobi_persistent"]["rotations"] == before
+    h.close()
+
+
 @pytest.mark.parametrize("shape", [(65, 63, 1), (63, 130, 1), (64, 64, 1), (3, 200, 1)])
 @pytest.mark.parametrize("fp32", [False, True])
 def test_matrix_transforms(shape, fp32):
