@@ -133,18 +133,15 @@ struct SeedState {
 };
 
 // A remaining norm is recomputed from its column under 1e-6 of its last
-// computed value.  Those are kept in FP32 relative to the power of two next to
+// computed value.  Those are kept in FP32 over 2^e, the power of two next to
 // ||A||_F^2, so that the steps are the same at every scale of the data (as they
 // come they are 0 for entries under 1e-23, where no norm would be recomputed,
-// and infinite over 1e19, where every one would at every step).
-struct SeedScale {
-    double inv;   // over the power of two
-    double lim;   // 1e-6 times it
-};
-
+// and infinite over 1e19, where every one would at every step).  e and stop2
+// (the rounding level of the norms) are scalar: the columns fill the vector
+// registers.
 // Steps j >= 16 K0; returns the steps done.
 template <int R, int S, int K0>
-__device__ __forceinline__ int seed_steps(SeedState<R, S>& st, SeedShared& sh, int n, double stop2, SeedScale sc,
+__device__ __forceinline__ int seed_steps(SeedState<R, S>& st, SeedShared& sh, int n, double stop2, int e,
                                           cplx<double>* G) {
     const int lane = threadIdx.x & 63, l = lane & 15, row = threadIdx.x >> 4;
     const int j1 = min(16 * (K0 + 1), n);
@@ -222,11 +219,11 @@ __device__ __forceinline__ int seed_steps(SeedState<R, S>& st, SeedShared& sh, i
             const double t = st.x[i][K0].re * st.x[i][K0].re + st.x[i][K0].im * st.x[i][K0].im;
             double c = st.cn[i];
             if (c > 0.0) c = fmax(c - __shfl(t, (lane & 48) | jl), 0.0);
-            if (__any(c >= 0.0 && c < sc.lim * st.cref[i])) {
+            if (__any(c >= 0.0 && c < 1e-6 * ldexp((double)st.cref[i], e))) {
                 const double nn = tail_norm2<R, K0>(st.x[i], l, j + 1);
                 if (c >= 0.0) {
                     c = nn;
-                    st.cref[i] = (float)(sc.inv * nn);
+                    st.cref[i] = (float)ldexp(nn, -e);
                 }
             }
             st.cn[i] = c;
@@ -236,11 +233,11 @@ __device__ __forceinline__ int seed_steps(SeedState<R, S>& st, SeedShared& sh, i
 }
 
 template <int R, int S, int K0 = 0>
-__device__ __forceinline__ int seed_all(SeedState<R, S>& st, SeedShared& sh, int n, double stop2, SeedScale sc,
+__device__ __forceinline__ int seed_all(SeedState<R, S>& st, SeedShared& sh, int n, double stop2, int e,
                                         cplx<double>* G) {
-    const int d = seed_steps<R, S, K0>(st, sh, n, stop2, sc, G);
+    const int d = seed_steps<R, S, K0>(st, sh, n, stop2, e, G);
     if (d >= 0 || n <= 16 * (K0 + 1)) return d < 0 ? n : d;
-    if constexpr (K0 + 1 < R) return seed_all<R, S, K0 + 1>(st, sh, n, stop2, sc, G);
+    if constexpr (K0 + 1 < R) return seed_all<R, S, K0 + 1>(st, sh, n, stop2, e, G);
     return n;
 }
 
@@ -306,11 +303,11 @@ __global__ __launch_bounds__(kSeedThreads) void jacobi_seed_kernel(const cplx<do
         __syncthreads();
         double f2 = 0.0;
         for (int w = 0; w < kSeedRows; ++w) f2 += fro[w];
-        const int e = f2 > kSeedTiny ? ilogb(f2) : 0;
-        const SeedScale sc{ldexp(1.0, -e), ldexp(1e-6, e)};
+        const int e = __builtin_amdgcn_readfirstlane(f2 > kSeedTiny ? ilogb(f2) : 0);
 #pragma unroll
-        for (int i = 0; i < S; ++i) st.cref[i] = (float)(sc.inv * st.cn[i]);
-        done = seed_all<R, S>(st, sh, n, fmax(4.93e-32 * f2, kSeedTiny), sc, g);   // eps^2 ||A||_F^2
+        for (int i = 0; i < S; ++i) st.cref[i] = (float)ldexp(st.cn[i], -e);
+        const double stop2 = lane_f64(fmax(4.93e-32 * f2, kSeedTiny), 0);   // eps^2 ||A||_F^2
+        done = seed_all<R, S>(st, sh, n, stop2, e, g);
     }
     __syncthreads();   // the reflectors of every wave are in memory
     constexpr int QS = (16 * R + kSeedRows - 1) / kSeedRows;
