@@ -605,7 +605,7 @@ SweepStats run_gram(tsvd_handle h, const Geometry& g, const SvtBuffers<float>& s
         square_gemm(h, K_GEMM, g, b.vprev, 1, b.vprev, 0, b.rv);
         square_gemm(h, K_GEMM, g, b.vprev, 0, b.rv, 0, b.v, nullptr, b.vprev, -0.5, 1.5);
     } else {
-        prof_launch(h, K_OTHER, 0.0, [&] { launch_jacobi_seed(b.r, b.v, b.rv, g.n, g.n, g.h, st); });
+        prof_launch(h, K_OTHER, 0.0, [&] { launch_jacobi_seed(b.r, b.v, b.rv, g.n, g.n, g.h, nullptr, st); });
         launch_check("jacobi_seed");
     }
     square_gemm(h, K_GEMM, g, b.r, 0, b.v, 0, b.rv);
@@ -758,7 +758,7 @@ SweepStats run_svt(tsvd_handle h, const Geometry& g, const SvtBuffers<T>& sb, in
     bool seeded = false;
     if constexpr (sizeof(T) == 8) {
         if (!warm && env_int("TSVD_SEED", 1) != 0 && jacobi_seed_fits(g.m, g.n)) {
-            prof_launch(h, K_OTHER, 0.0, [&] { launch_jacobi_seed(sb.A, sb.V[vc], sb.G, g.m, g.n, g.h, st); });
+            prof_launch(h, K_OTHER, 0.0, [&] { launch_jacobi_seed(sb.A, sb.V[vc], sb.G, g.m, g.n, g.h, h->flag + 1, st); });
             launch_check("jacobi_seed");
             seeded = true;
         }
@@ -993,7 +993,7 @@ LoopResult admm_loop(tsvd_handle h, int max_iter, F&& iteration) {
     return r;
 }
 
-void clear_flag(tsvd_handle h) { launch_fill<int>(h->flag, 0, 1, h->stream); }
+void clear_flag(tsvd_handle h) { launch_fill<int>(h->flag, 0, 2, h->stream); }
 
 // Words of the one-launch Jacobi sweeps, cleared once per call (then by the end
 // of every SVD, but for the error word).  Error word, pbar[h]: bit 1 (a wait
@@ -1583,7 +1583,7 @@ tsvd_status tsvd_create(int device, size_t hbm_budget_bytes, tsvd_handle* out) {
         h->lds_cap = lds_max > 0 ? (size_t)lds_max : 65536;
         h->budget = hbm_budget_bytes;
         hipError_t e = hipMalloc(reinterpret_cast<void**>(&h->ctrl), sizeof(Ctrl));
-        if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&h->flag), sizeof(int));
+        if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&h->flag), 2 * sizeof(int));
         if (e == hipSuccess) e = hipHostMalloc(reinterpret_cast<void**>(&h->host_ctrl), sizeof(Ctrl), 0);
         if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&h->rot_counter), 2 * sizeof(unsigned long long));
         if (e == hipSuccess) e = hipMemset(h->rot_counter, 0, 2 * sizeof(unsigned long long));

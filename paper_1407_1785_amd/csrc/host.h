@@ -90,7 +90,7 @@ struct tsvd_handle_s {
     size_t ws_bytes = 0;
     // small device objects
     tsvd::Ctrl* ctrl = nullptr;
-    int* flag = nullptr;            // non-finite flag
+    int* flag = nullptr;            // non-finite flag; whether a cold FP64 SVD takes the QR start
     void* dmat = nullptr;           // DFT matrices of the current tube shape
     int64_t dmat_key = -1;          // (P, Q, element size) they were built for
     // pinned host staging

@@ -326,9 +326,11 @@ TallPlan jacobi_tall_plan(int m, int n, int h);
 template <typename T>
 void launch_jacobi_tall_round(const JacArgs<T>& a, const TallPlan& t, double* part, hipStream_t st);
 // Start V of a cold FP64 SVD (seed.hip): V = Q of the pivoted QR of A^H, per
-// slice; G is n x n scratch per slice.
+// slice; G is n x n scratch per slice.  alike: a word that is 0 before the
+// call, with which data that gain nothing from the QR get V = I; null: the QR
+// always.
 bool jacobi_seed_fits(int m, int n);
-void launch_jacobi_seed(const cplx<double>* A, cplx<double>* V, cplx<double>* G, int m, int n, int h,
+void launch_jacobi_seed(const cplx<double>* A, cplx<double>* V, cplx<double>* G, int m, int n, int h, int* alike,
                         hipStream_t st);
 // Tall FP32 slices through their FP64 Gram matrix (tall.hip).
 constexpr int kMaxGramCols = 96;
