@@ -41,8 +41,6 @@ namespace {
 
 using namespace jac;
 
-constexpr int kPGs = 32;
-
 // All sweeps of slice s by this workgroup.
 template <typename T, int BW, int RPT>
 __device__ __forceinline__ void slice_svd(const JacSliceArgs<T>& a, int s, int max_sweeps) {
@@ -304,10 +302,6 @@ __global__ __launch_bounds__(BW * kPGs, (jacobi_waves_per_simd<T, kPGs, BW, RPT>
 
 }  // namespace
 
-// The launches of one element type and block width, each instantiated in a
-// source of its own (jacobi_slice_*.hip).
-enum class SliceOp { PREPARE, SLICE, PAIRS };
-
 // PREPARE: set the LDS limit of both kernels.  SLICE: x = max_sweeps.
 // PAIRS: words and x = spin_limit.
 template <typename T, int BW, int RPT>
@@ -329,10 +323,6 @@ hipError_t slice_op_rpt(SliceOp op, const JacSliceArgs<T>* tab, const int* start
         hipLaunchKernelGGL(fp, dim3(nwg), dim3(BW * kPGs), lds, st, tab, start, nprob, words, x);
     return hipGetLastError();
 }
-
-template <typename T, int BW>
-hipError_t slice_op(SliceOp op, int rpt, const JacSliceArgs<T>* tab, const int* start, int nprob, int nwg, int* words,
-                    int x, hipStream_t st);
 
 template <typename T, int BW, int... R>
 hipError_t slice_op_seq(SliceOp op, int rpt, std::integer_sequence<int, R...>, const JacSliceArgs<T>* tab,

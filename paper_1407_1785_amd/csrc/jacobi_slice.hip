@@ -5,15 +5,7 @@
 
 namespace tsvd {
 
-enum class SliceOp { PREPARE, SLICE, PAIRS };
-
-template <typename T, int BW>
-hipError_t slice_op(SliceOp op, int rpt, const JacSliceArgs<T>* tab, const int* start, int nprob, int nwg, int* words,
-                    int x, hipStream_t st);
-
 namespace {
-
-constexpr int kPGs = 32;
 
 template <typename T>
 hipError_t dispatch(SliceOp op, int bw, int rpt, const JacSliceArgs<T>* tab, const int* start, int nprob, int nwg,

@@ -221,6 +221,14 @@ struct JacSliceArgs {
     int* clr;
     int nclr;
 };
+// Lanes per column pair in jacobi_slice.h.
+constexpr int kPGs = 32;
+// The launches of one element type and block width, each instantiated in a
+// source of its own (jacobi_slice_*.hip) and reached through jacobi_slice.hip.
+enum class SliceOp { PREPARE, SLICE, PAIRS };
+template <typename T, int BW>
+hipError_t slice_op(SliceOp op, int rpt, const JacSliceArgs<T>* tab, const int* start, int nprob, int nwg, int* words,
+                    int x, hipStream_t st);
 // Doubles per problem of the pairs-parallel schedule's Frobenius parts (JacSliceArgs::fro).
 inline int64_t jacobi_pairs_fro(int h, int n) { return (int64_t)h * (n / 2 + 1); }
 // Ints per problem of the pairs-parallel schedule's barrier area (JacSliceArgs::bar).
