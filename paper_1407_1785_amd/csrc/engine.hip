@@ -566,6 +566,13 @@ private:
         return std::min(s, cus_);
     }
 
+    // Narrower blocks take twice the workgroups, which a class on its own does
+    // not feel and a batch does: they have to be faster by more than this.
+    // (Alone, 97 x 50 to 93 x 65 FP64 slices tie within 7%, 0.081 to 0.102 ms a
+    // sweep; batches that took the narrower blocks there ran 27.8 and 45.4 ms,
+    // with 16 columns 23.3 and 36.1.)
+    static constexpr float kNarrowerGain = 0.85f;
+
     // Time every candidate on S synthetic slices of this shape (pseudo-random
     // entries, V = I, one sweep) and keep the fastest.
     TuneChoice tune(int m, int n, int rpt, int S, const std::vector<TuneChoice>& cand) {
@@ -638,7 +645,7 @@ private:
                 if (env_int("TSVD_TUNE_LOG", 0))
                     std::fprintf(stderr, "[tsvd tune] m=%d n=%d rpt=%d slices=%d bw=%d pairs=%d: %.3f ms\n", m, n, rpt, S, c.bw,
                                  c.pairs ? 1 : 0, ms);
-                if (ms < best_ms) {
+                if (ms < (c.bw < best.bw ? kNarrowerGain : 1.f) * best_ms) {
                     best_ms = ms;
                     best = c;
                 }

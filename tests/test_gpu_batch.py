@@ -309,3 +309,22 @@ def test_widest_classes_against_oracle(widest, dt):
             assert_close_fp32(got, ref, FP32_BAR, str(d["M_obs"].shape))
         else:
             assert rel_fro(got, ref) <= FP64_BAR, d["M_obs"].shape
+
+
+def test_tuner_keeps_wide_blocks(tmp_path, monkeypatch):
+    """FP64 slices of 50 to 65 columns, where blocks of 8 and of 16 columns tie
+    within some percent: the tuner keeps 16, which take half the workgroups.
+    (One slice a problem: classes no other test times.)"""
+    torch = torch_cuda()
+    path = tmp_path / "tune.txt"
+    monkeypatch.setenv("TSVD_AUTOTUNE_CACHE", str(path))
+    monkeypatch.delenv("TSVD_TUNE", raising=False)
+    cases = [(f"wide{i}", "complete", *_completion(s, 60 + i), np.float64, {})
+             for i, s in enumerate([(97, 50, 1), (76, 62, 1), (93, 65, 1), (140, 60, 1)])]
+    probs = [_problem(torch, c, iters=2) for c in cases]
+    announce("tuner: wide blocks")
+    h = lib.Handle(0, 1 << 28)
+    assert all(status == 0 for status, _ in lib.batch_run(probs, handle=h))
+    h.close()
+    lines = [ln.split() for ln in path.read_text().splitlines()]
+    assert len(lines) >= 3 and all(ln[6] == "16" for ln in lines), lines
