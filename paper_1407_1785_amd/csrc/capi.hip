@@ -637,7 +637,7 @@ SweepStats run_gram(tsvd_handle h, const Geometry& g, const SvtBuffers<float>& s
     prof_launch(h, K_SVT_W, (double)vv * sizeof(cplx<double>) + (double)g.h * g.n * sizeof(double), [&] {
         hip_check(launch_jacobi_slice<double>(16, jacobi_slice_rpt(g.n, g.n),
                                               reinterpret_cast<const JacSliceArgs<double>*>(sb.ftab), sb.fws, 1,
-                                              g.h * finish_parts(h, g), max_sweeps, st),
+                                              g.h * finish_parts(h, g), max_sweeps, false, st),
                   "jacobi fallback");
     });
     if (h->prof_on) stats.sweeps = record_sweeps(h, g, sb, ip, 48.0 * g.n);
@@ -833,7 +833,7 @@ SweepStats run_svt(tsvd_handle h, const Geometry& g, const SvtBuffers<T>& sb, in
         const int spin = std::max(0, env_int("TSVD_PERSIST_SPIN", 1 << 21));
         const int ip = prof_launch(h, K_JAC_PERSIST, 0.0, [&] {
             hip_check(launch_jacobi_pairs<T>(plan.bw, plan.rpt, sb.ftab + 4 + entry, sb.fws + 2, 1,
-                                             g.h * (plan.nb / 2), sb.pbar + g.h - 1, spin, st),
+                                             g.h * (plan.nb / 2), sb.pbar + g.h - 1, spin, false, st),
                       "jacobi block pairs");
         });
         done_persist = true;
@@ -887,7 +887,7 @@ SweepStats run_svt(tsvd_handle h, const Geometry& g, const SvtBuffers<T>& sb, in
         if (stats.on_device)
             // with the sweeps that a launch whose waits gave up has left
             hip_check(launch_jacobi_slice<T>(plan.bw, plan.rpt, sb.ftab + entry, sb.fws, 1,
-                                             g.h * finish_parts(h, g), max_sweeps, st),
+                                             g.h * finish_parts(h, g), max_sweeps, false, st),
                       "jacobi fallback");
         else
             launch_svt_sigma(work, g.m, g.n, g.h, sb.sigma, sb.dk, h->ctrl, st);

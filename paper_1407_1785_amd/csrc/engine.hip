@@ -215,6 +215,7 @@ struct Tables {
     };
     Phase fwd, gram, ns, pre, sig, reb, inv, ctl;
     std::vector<Phase> jac;
+    bool spread = false;   // Jacobi classes: one workgroup per CU
     std::vector<char> host;
     char* dev = nullptr;
     size_t dev_cap = 0;
@@ -623,10 +624,10 @@ private:
                     launch_fill<int>(words, 0, (int64_t)ints, stream_);
                     hip_check(hipEventRecord(e0, stream_), "hipEventRecord");
                     if (c.pairs)
-                        hip_check(launch_jacobi_pairs<T>(c.bw, rpt, dtab, dws, 1, S * G, words, 1 << 21, stream_),
+                        hip_check(launch_jacobi_pairs<T>(c.bw, rpt, dtab, dws, 1, S * G, words, 1 << 21, false, stream_),
                                   "jacobi tuner launch");
                     else
-                        hip_check(launch_jacobi_slice<T>(c.bw, rpt, dtab, dws, 1, S, 1, stream_),
+                        hip_check(launch_jacobi_slice<T>(c.bw, rpt, dtab, dws, 1, S, 1, false, stream_),
                                   "jacobi tuner launch");
                     hip_check(hipEventRecord(e1, stream_), "hipEventRecord");
                     hip_check(hipEventSynchronize(e1), "hipEventSynchronize");
@@ -885,6 +886,15 @@ private:
             ph.lane = best;
             load[best] += ph.work;
         }
+        // The classes' launches on several streams put two workgroups on a CU while
+        // others idle: as long as there is about a CU for every workgroup, they
+        // reserve one each.  33 to 256 workgroups: 0 to 20% faster than two to a CU (three FP64 problems to 189
+        // x 93 x 31, 129 workgroups, 32.8 -> 27.7 ms); 265 and 280: 11 and 13%; but
+        // 344 5%, 438 9% and the 2239 of twelve problems 31% slower.
+        // TSVD_BATCH_SPREAD=0 never, =1 always.
+        int64_t total = 0;
+        for (const auto& ph : tb.jac) total += ph.nwg;
+        tb.spread = env_int("TSVD_BATCH_SPREAD", 4 * total <= 5 * (int64_t)cus_) != 0;
         if (tb.host.size() > tb.dev_cap) {
             if (tb.dev) hip_check(hipFree(tb.dev), "hipFree tables");
             tb.dev = nullptr;
@@ -926,11 +936,11 @@ private:
             const auto& ph = tb.jac[c];
             if (ph.pairs)
                 hip_check(launch_jacobi_pairs<T>(ph.bw, ph.rpt, targs<JacSliceArgs<T>>(tb, ph), tws(tb, ph), ph.nprob,
-                                                 ph.nwg, words_ + 2 * c, spin, side_[ph.lane]),
+                                                 ph.nwg, words_ + 2 * c, spin, tb.spread, side_[ph.lane]),
                           "batched jacobi pairs");
             else
                 hip_check(launch_jacobi_slice<T>(ph.bw, ph.rpt, targs<JacSliceArgs<T>>(tb, ph), tws(tb, ph),
-                                                 ph.nprob, ph.nwg, 30, side_[ph.lane]),
+                                                 ph.nprob, ph.nwg, 30, tb.spread, side_[ph.lane]),
                           "batched jacobi");
         }
         for (int k = 0; k < kLanes; ++k)

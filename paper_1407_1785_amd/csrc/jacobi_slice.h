@@ -35,6 +35,8 @@
 
 #include "jacobi_common.h"
 
+#include <algorithm>
+
 namespace tsvd {
 
 namespace {
@@ -306,10 +308,11 @@ __global__ __launch_bounds__(BW * kPGs, (jacobi_waves_per_simd<T, kPGs, BW, RPT>
 // PAIRS: words and x = spin_limit.
 template <typename T, int BW, int RPT>
 hipError_t slice_op_rpt(SliceOp op, const JacSliceArgs<T>* tab, const int* start, int nprob, int nwg, int* words, int x,
-                        hipStream_t st) {
+                        bool spread, hipStream_t st) {
     auto* fs = jacobi_slice_kernel<T, BW, RPT>;
     auto* fp = jacobi_pairs_kernel<T, BW, RPT>;
-    const size_t lds = jacobi_slice_lds(BW, RPT, sizeof(T));
+    const size_t own = jacobi_slice_lds(BW, RPT, sizeof(T));
+    const size_t lds = op == SliceOp::PREPARE || spread ? std::max(own, kSpreadLds) : own;
     if (op == SliceOp::PREPARE) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fs),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -326,18 +329,19 @@ hipError_t slice_op_rpt(SliceOp op, const JacSliceArgs<T>* tab, const int* start
 
 template <typename T, int BW, int... R>
 hipError_t slice_op_seq(SliceOp op, int rpt, std::integer_sequence<int, R...>, const JacSliceArgs<T>* tab,
-                        const int* start, int nprob, int nwg, int* words, int x, hipStream_t st) {
+                        const int* start, int nprob, int nwg, int* words, int x, bool spread,
+                        hipStream_t st) {
     hipError_t e = hipErrorInvalidValue;
-    ((rpt == R + 2 ? (e = slice_op_rpt<T, BW, R + 2>(op, tab, start, nprob, nwg, words, x, st), 0) : 0), ...);
+    ((rpt == R + 2 ? (e = slice_op_rpt<T, BW, R + 2>(op, tab, start, nprob, nwg, words, x, spread, st), 0) : 0), ...);
     return e;
 }
 
 #define TSVD_SLICE_INSTANCE(T, BW)                                                                                   \
     template <>                                                                                                      \
     hipError_t slice_op<T, BW>(SliceOp op, int rpt, const JacSliceArgs<T>* tab, const int* start, int nprob, int nwg, \
-                               int* words, int x, hipStream_t st) {                                                  \
+                               int* words, int x, bool spread, hipStream_t st) {                                     \
         return slice_op_seq<T, BW>(op, rpt, std::make_integer_sequence<int, 19>{}, tab, start, nprob, nwg, words, x, \
-                                   st);                                                                              \
+                                   spread, st);                                                                      \
     }
 
 }  // namespace tsvd

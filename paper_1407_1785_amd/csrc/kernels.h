@@ -228,7 +228,9 @@ constexpr int kPGs = 32;
 enum class SliceOp { PREPARE, SLICE, PAIRS };
 template <typename T, int BW>
 hipError_t slice_op(SliceOp op, int rpt, const JacSliceArgs<T>* tab, const int* start, int nprob, int nwg, int* words,
-                    int x, hipStream_t st);
+                    int x, bool spread, hipStream_t st);
+// Over half of a CU's LDS: workgroups that reserve it do not share a CU.
+constexpr size_t kSpreadLds = 160 * 1024 / 2 + 1024;
 // Doubles per problem of the pairs-parallel schedule's Frobenius parts (JacSliceArgs::fro).
 inline int64_t jacobi_pairs_fro(int h, int n) { return (int64_t)h * (n / 2 + 1); }
 // Ints per problem of the pairs-parallel schedule's barrier area (JacSliceArgs::bar).
@@ -242,7 +244,7 @@ template <typename T>
 hipError_t prepare_jacobi_slice(int bw, int rpt);
 template <typename T>
 hipError_t launch_jacobi_slice(int bw, int rpt, const JacSliceArgs<T>* tab, const int* wg_start, int nprob,
-                               int nwg, int max_sweeps, hipStream_t st);
+                               int nwg, int max_sweeps, bool spread, hipStream_t st);
 // Pairs-parallel schedule over a problem table: one launch runs every sweep
 // of every slice, nb / 2 workgroups per slice (one per block pair of a round)
 // exchanging blocks between rounds; workgroups take their roles in order from
@@ -251,7 +253,7 @@ hipError_t launch_jacobi_slice(int bw, int rpt, const JacSliceArgs<T>* tab, cons
 // role_start: nprob + 1 cumulative role counts (h nb / 2 per problem).
 template <typename T>
 hipError_t launch_jacobi_pairs(int bw, int rpt, const JacSliceArgs<T>* tab, const int* role_start, int nprob,
-                               int nroles, int* words, int spin_limit, hipStream_t st);
+                               int nroles, int* words, int spin_limit, bool spread, hipStream_t st);
 
 template <typename T>
 struct SigmaArgs {

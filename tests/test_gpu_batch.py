@@ -4,6 +4,7 @@ oracle and against the single-problem calls; HIP-graph replay against eager
 launches."""
 
 import os
+import time
 
 import numpy as np
 import pytest
@@ -328,3 +329,38 @@ def test_tuner_keeps_wide_blocks(tmp_path, monkeypatch):
     h.close()
     lines = [ln.split() for ln in path.read_text().splitlines()]
     assert len(lines) >= 3 and all(ln[6] == "16" for ln in lines), lines
+
+
+def test_small_batches_take_a_cu_per_workgroup(monkeypatch):
+    """Three problems of some 130 workgroups on three streams: reserving a CU
+    each gives the same bits as sharing, also when forced on a batch of one
+    workgroup a slice and of several classes, and is what such a batch does
+    (it is 15% faster)."""
+    torch = torch_cuda()
+    cases = [(f"spread{i}", "complete", *_completion(s, 80 + i), np.float64, {})
+             for i, s in enumerate([(151, 77, 27), (189, 93, 31), (122, 84, 24)])]
+    small = [c for c in _cases() if c[1] == "complete" and c[4] == np.float64]
+    out, best = {}, {}
+    for mode in ("0", "1", ""):
+        if mode:
+            monkeypatch.setenv("TSVD_BATCH_SPREAD", mode)
+        else:
+            monkeypatch.delenv("TSVD_BATCH_SPREAD")
+        announce("batch spread", mode or "rule")
+        h = lib.Handle(0, 1 << 30)
+        probs = [_problem(torch, c, iters=20) for c in cases]
+        best[mode] = np.inf
+        for _ in range(4):
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            assert all(status == 0 for status, _ in lib.batch_run(probs, handle=h))
+            torch.cuda.synchronize()
+            best[mode] = min(best[mode], time.perf_counter() - t)
+        others = [_problem(torch, c) for c in small]
+        assert all(status == 0 for status, _ in lib.batch_run(others, handle=h))
+        out[mode] = [p.out.cpu().numpy() for p in probs + others]
+        h.close()
+    for a, b, c in zip(out["0"], out["1"], out[""]):
+        np.testing.assert_array_equal(a, b)
+        np.testing.assert_array_equal(a, c)
+    assert best[""] < 0.95 * best["0"], best
