@@ -207,8 +207,8 @@ JacPlan jacobi_plan(tsvd_handle h, const Geometry& g) {
 }
 
 // Tall FP32 slices of few columns take their SVD from the FP64 Gram matrix
-// (tall.hip): up to kMaxGramCols columns (the Cholesky factor's LDS), at least
-// 12 n rows (the n x n matrices and the chunk sums live in the second slice
+// (tall.hip): up to kMaxGramCols columns (the register tiles of its product and
+// of its Cholesky factorisation), at least 12 n rows (the n x n matrices and the chunk sums live in the second slice
 // buffer, which the thresholded slice takes last), and where the n x n problem
 // fits the persistent Jacobi.  TSVD_GRAM=0 keeps the global-memory Jacobi,
 // which wider and FP64 slices take.

@@ -17,7 +17,7 @@
 //
 // gram_partial: one workgroup per chunk of rows, the chunk staged through LDS
 // 64 rows at a time, FP64 16 x 16 x 4 matrix products over the tiles on and
-// above the diagonal (one real product for a matrix, three for a complex slice).
+// above the diagonal (one real product for a matrix, four for a complex slice).
 // Bound: the FP64 matrix rate (8 m n^2 flops halved by symmetry; a 20480 x 64
 // matrix is 0.17 GFLOP) beside one read of the slice.
 //
@@ -38,6 +38,11 @@ typedef double v4d __attribute__((ext_vector_type(4)));
 
 constexpr int kGramRows = 64;                  // rows staged at a time
 constexpr int kGramLd = kGramRows + 2;         // LDS column stride (elements)
+constexpr int kGramTiles = 6;                  // 16 x 16 tiles a wave accumulates
+static_assert(kMaxGramCols / 16 * (kMaxGramCols / 16 + 1) / 2 <= kGramTiles * (kBlock / 64) &&
+                  kMaxGramCols % 16 == 0,
+              "the tiles on and above the diagonal fit the waves' accumulators");
+static_assert(kMaxGramCols * kGramLd * sizeof(cplx<float>) <= 64 * 1024, "the staged rows fit the default LDS limit");
 
 // partial[(chunk * h + s) * n^2 + col * n + row], every entry of the n x n
 // matrix of chunk `chunk` of slice s.
@@ -51,13 +56,11 @@ __global__ __launch_bounds__(kBlock) void gram_partial_kernel(const cplx<float>*
     const int r0 = chunk * rows_per, r1 = min(r0 + rows_per, m);
     const cplx<float>* const a = A + (int64_t)s * n * m;
     const int nt = (n + 15) / 16, np = nt * 16;
-    const int ntile = nt * (nt + 1) / 2;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int c16 = lane & 15, kq = lane >> 4;
-    constexpr int kMaxT = 6;                    // tiles per wave: n <= 96 has 21
-    v4d re[kMaxT], im[kMaxT];
+    v4d re[kGramTiles], im[kGramTiles];
 #pragma unroll
-    for (int i = 0; i < kMaxT; ++i) re[i] = im[i] = v4d{0.0, 0.0, 0.0, 0.0};
+    for (int i = 0; i < kGramTiles; ++i) re[i] = im[i] = v4d{0.0, 0.0, 0.0, 0.0};
     for (int b0 = r0; b0 < r1; b0 += kGramRows) {
         __syncthreads();
         // rows past the chunk and columns past n are zero
@@ -86,7 +89,7 @@ __global__ __launch_bounds__(kBlock) void gram_partial_kernel(const cplx<float>*
                     }
                 }
 #pragma unroll
-                for (int i = 0; i < kMaxT; ++i)
+                for (int i = 0; i < kGramTiles; ++i)
                     if (i == t) {
                         re[i] += tr;
                         if (!REAL) im[i] += tm;
@@ -101,7 +104,7 @@ __global__ __launch_bounds__(kBlock) void gram_partial_kernel(const cplx<float>*
             if ((ix & 3) != wave) continue;
             v4d tr = v4d{0.0, 0.0, 0.0, 0.0}, tm = tr;
 #pragma unroll
-            for (int i = 0; i < kMaxT; ++i)
+            for (int i = 0; i < kGramTiles; ++i)
                 if (i == t) {
                     tr = re[i];
                     tm = im[i];
@@ -115,7 +118,6 @@ __global__ __launch_bounds__(kBlock) void gram_partial_kernel(const cplx<float>*
                 if (ti != tj) out[(int64_t)i * n + j] = cplx<double>{tr[v], -tm[v]};
             }
         }
-    (void)ntile;
 }
 
 // G = sum of the chunks in a fixed order: four threads per entry.
@@ -152,6 +154,8 @@ __global__ __launch_bounds__(kBlock) void gram_sum_kernel(const cplx<double>* pa
 // every wave subtracts its product.  With the matrix in LDS and two barriers
 // a step the factorisation of a 64 x 64 matrix took 142 us.
 constexpr int kCholThreads = 512, kCholWaves = kCholThreads / 64;
+static_assert(kMaxGramCols <= 2 * 64 && kMaxGramCols % kCholWaves == 0,
+              "two rows a lane and whole columns a wave hold the largest matrix");
 
 template <int CTRL>
 __device__ __forceinline__ double dpp_max(double v) {
