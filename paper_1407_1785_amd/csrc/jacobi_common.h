@@ -357,8 +357,12 @@ __device__ __forceinline__ int slice_meet(int* word, int G, const int* vote, uns
 // Cross steps wave to wave: a wave finishes step st + 1 only after its
 // successor wave (cyclically) has finished step st, whose column it reads
 // next; each wave counts its finished steps in LDS (release after its LDS
-// writes, acquire before its reads).  Every wave of the workgroup runs every
-// step, so the waits end; the bound only guards against a fault.
+// writes, acquire before its reads).  Every wave of the ring runs every step of
+// a round, so the waits end; the bound only guards against a fault.  Waves
+// without columns (a block of 12 columns fills six of eight waves) are not in
+// the ring of the cross steps: none waits for them there, and a count that
+// stayed behind is waited on again only after its wave has published steps of
+// a later round, whose numbers start from the same `steps` in every wave.
 __device__ __forceinline__ void ring_publish(int* cnt, int value) {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     if ((threadIdx.x & 63) == 0) __hip_atomic_store(cnt, value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);

@@ -83,9 +83,9 @@ __device__ bool wait_flag(int* flag, int value, int* err, int spin_limit) {
 // else.  Each wave counts its finished steps in LDS (release after its LDS
 // writes); a wave waits for its successor's count (acquire) instead of a
 // workgroup barrier, so a step costs the waves' average rather than the
-// slowest pair.  Every wave of the workgroup runs every step of a round
-// (giving up happens only between rounds), so a wait lasts at most a few
-// steps.  One that runs far longer means a fault: the wave stops waiting
+// slowest pair.  Every wave of the ring runs every step of a round (giving up
+// happens only between rounds; waves without columns are not in it), so a wait
+// lasts at most a few steps.  One that runs far longer means a fault: the wave stops waiting
 // and sets the error word to 2, which fails the call (the block data can no
 // longer be trusted); it checks the error word every 1024 polls, so after
 // such a fault no wait spins to its cap again.

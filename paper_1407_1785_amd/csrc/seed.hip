@@ -23,7 +23,8 @@
 // Q = H_0 ... H_{n-1} is accumulated backwards, the columns of Q in
 // registers, without barriers.  The steps end early once no remaining column
 // is above the rounding level eps ||A||_F: the columns of A Q they would
-// order are below the stopping rule's floor.
+// order are below the stopping rule's floor.  Tensors whose columns are not
+// alike (columns_alike_kernel) keep V = I.
 //
 // Bound: vector issue of the reflections (two waves per SIMD) and, once a
 // step, the owner's serial chain between two barriers.  With a column per

@@ -12,7 +12,8 @@
 // to sqrt(eps64) = 1.5e-8 of the largest, under the FP32 rounding of A's own
 // entries, so V and sigma come out closer to the exact ones than the FP32
 // rotations left them.  The thresholded slice is A (V diag(d) V^H), one
-// product.  In FP64 the Gram matrix would lose half the digits, so FP64
+// product; where the left vectors are asked for, A V is swept orthogonal once
+// more (left_vectors in capi.hip).  In FP64 the Gram matrix would lose half the digits, so FP64
 // unfoldings keep the global-memory Jacobi (jacobi.hip).
 //
 // gram_partial: one workgroup per chunk of rows, the chunk staged through LDS
