@@ -138,14 +138,16 @@ struct PRot {
     bool on;
 };
 
-// The pair is rotated when |gamma|^2 > tol^2 alpha beta (and kMinGamma2, or 0 in
-// the FP32 form, whose gamma cannot come near it).  As one comparison with the
-// larger bound: with two, the second against a 64-bit constant, a 128 x 160 x 64
-// FP64 completion was 0.6% slower.
+// The pair is rotated when |gamma|^2 > tol^2 alpha beta, and where that is not
+// (much) larger, kMinGamma2; 0 in the FP32 form, whose gamma cannot come near
+// it.  The sum of the two bounds costs no instruction (a tracked alpha may be
+// rounded below 0: then d^2 alone is normal and a rotation by 0 is exact).  As a
+// comparison of its own, against a 64-bit constant, it was 0.6% of a 128 x 160 x
+// 64 FP64 completion, as the larger of both 1% of a 96 x 128 x 3 x 48 prox.
 template <typename T>
 __device__ __forceinline__ bool prot_needed(double al, double be, double g2, double tol) {
     if constexpr (sizeof(T) == 4) return g2 > (tol * tol) * al * be && g2 > 0.0;
-    return g2 > fmax((tol * tol) * al * be, kMinGamma2);
+    return g2 > fma((tol * tol) * al, be, kMinGamma2);
 }
 
 // The rotation through d = beta - alpha and r = sqrt(d^2 + 4 |gamma|^2)
