@@ -33,14 +33,16 @@ def smooth(rng, m, n, n3):
 
 
 @pytest.mark.parametrize("size", SIZES)
-@pytest.mark.parametrize("kind", ["noise", "smooth"])
+@pytest.mark.parametrize("kind", ["noise", "smooth", "one slice"])
 def test_seeded_prox_matches_oracle(size, kind):
     torch = torch_cuda()
     m, n = size
     rng = np.random.default_rng(m * 1000 + n)
-    x = rng.normal(size=(m, n, 4)) if kind == "noise" else smooth(rng, m, n, 4)
+    x = smooth(rng, m, n, 4) if kind == "smooth" else rng.normal(size=(m, n, 4))
+    if kind == "one slice":   # noise that takes the QR for one slice's sake
+        x += 10.0 * np.outer(rng.normal(size=m), rng.normal(size=n))[:, :, None]
     sv = np.linalg.svd(x.sum(axis=2), compute_uv=False)
-    k = len(sv) // 2 if kind == "noise" else min(4, len(sv) - 1)
+    k = min(4, len(sv) - 1) if kind == "smooth" else len(sv) // 2
     tau = float(0.5 * (sv[k - 1] + sv[k])) + 1e-9 * sv[0]
     z_ref, _ = tsvt_oracle(x, tau)
     for data, ref in ((x, z_ref), (x.transpose(1, 0, 2), z_ref.transpose(1, 0, 2))):
