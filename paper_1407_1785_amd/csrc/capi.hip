@@ -760,7 +760,8 @@ SweepStats run_svt(tsvd_handle h, const Geometry& g, const SvtBuffers<T>& sb, in
     bool seeded = false;
     if constexpr (sizeof(T) == 8) {
         if (!warm && env_int("TSVD_SEED", 1) != 0 && jacobi_seed_fits(g.m, g.n)) {
-            prof_launch(h, K_OTHER, 0.0, [&] { launch_jacobi_seed(sb.A, sb.V[vc], sb.G, g.m, g.n, g.h, h->flag + 1, st); });
+            prof_launch(h, K_OTHER, 0.0,
+                        [&] { launch_jacobi_seed(sb.A, sb.V[vc], sb.G, g.m, g.n, g.h, h->flag + 1, st); });
             launch_check("jacobi_seed");
             seeded = true;
         }
