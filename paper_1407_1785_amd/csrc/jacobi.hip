@@ -480,7 +480,9 @@ int jacobi_block_width(int m, int n, int elem_bytes, int h) {
     if (pick_rpt(rows) < 0) return -1;
     int best = -1;
     for (int bw : {16, 8, 4}) {
-        if ((size_t)bw * rows * 2 * elem_bytes > g_lds_cap) continue;
+        // with room for the kernels' own words: blocks of 16 FP64 columns of 640
+        // rows are the whole LDS, and such a launch aborts the queue
+        if ((size_t)bw * rows * 2 * elem_bytes + 64 > g_lds_cap) continue;
         if (best < 0) best = bw;
         const int nb = jacobi_num_blocks(n, bw);
         if ((int64_t)(nb / 2) * h >= 128) return bw;

@@ -64,3 +64,16 @@ def test_few_columns_many_rows(size):
     ref, rank_ref = tsvt_oracle(x, tau)
     assert rel_fro(z.cpu().numpy(), ref) <= 1e-12 and ranks == list(rank_ref)
     assert "jacobi_persistent" in kinds and "jacobi_cross" not in kinds
+
+
+@pytest.mark.parametrize("size", [(613, 27, 1), (540, 100, 2), (320, 320, 2)])
+def test_blocks_as_large_as_the_lds(size):
+    """Stacked columns of 640 rows in FP64: 16 of them are the whole LDS, which
+    leaves none for the kernels' own words, so narrower blocks run."""
+    torch = torch_cuda()
+    x = np.random.default_rng(size[0]).normal(size=size)
+    tau = 0.7 * np.sqrt(size[0])
+    announce("largest blocks", size)
+    z, ranks = lib.tsvt(to_gpu(torch, x), tau)
+    ref, rank_ref = tsvt_oracle(x, tau)
+    assert rel_fro(z.cpu().numpy(), ref) <= 1e-12 and ranks == list(rank_ref)
